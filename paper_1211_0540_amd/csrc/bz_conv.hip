@@ -9,9 +9,9 @@
 //   a step are contiguous; while a step runs, the next step's weights are
 //   copied HBM -> LDS by one coalesced direct-to-LDS load per 1 KiB
 //   (global_load_lds_dwordx4) into the other half of a per-wave double buffer,
-//   and the running step reads its weights with broadcast LDS reads.  (Reading
-//   them through the scalar cache instead leaves only a few 64-byte requests in
-//   flight and stalls every step on HBM latency.)  A work item is a range of
+//   and the running step reads its weights with broadcast LDS reads; from N = 28
+//   on the one-launch kernel reads them through the scalar cache instead, with
+//   the next step's weights pulled into L2 (cells_step_scalar).  A work item is a range of
 //   steps of one output row (k1, k2, 0..N-1) of 64 cells; it keeps
 //   the row's N accumulators and, per step (m1, m2), the rows fhat(m1, m2, .)
 //   and fhat(j1, j2, .) of its own cell in registers (cell-interleaved layout,
@@ -41,6 +41,9 @@
 //   (lane, m) is streamed from HBM in a coalesced layout, fhat_m is uniform and
 //   fhat_j is a per-lane read.  This is the paper's precompute-and-store
 //   organisation; it is bound by the weight stream.
+#include <type_traits>
+#include <utility>
+
 #include "bz_internal.h"
 
 namespace bz {
@@ -102,6 +105,84 @@ __device__ __forceinline__ void cells_step(const typename cplx<T>::t (&mv)[N], c
         pr[k3] += sr[0];
         pi[k3] += si[0];
     }
+}
+
+// Weights through scalar registers.  A VALU instruction takes a scalar operand for free, while a
+// broadcast LDS read returns its weights to every lane: 16 bytes to 64 lanes take 16 cycles of the
+// CU's LDS, which feed 24 operations, and the four SIMDs issue those in 13 (two wavefronts of a
+// SIMD issue one operation per 2 cycles together; one alone, one per 4).  The step's weights come
+// in chunks of CW by scalar loads, two chunks in registers: the next one is requested when the
+// current one has arrived (scalar loads return in any order, so a wait is a wait for all).
+template <typename T, int N>
+constexpr int weight_chunk() {
+    constexpr int PS = 3 * N * N / 4;
+    if (sizeof(T) == 8) return PS % 16 == 0 ? 16 : PS % 12 == 0 ? 12 : 4;
+    return PS % 32 == 0 ? 32 : PS % 24 == 0 ? 24 : PS % 28 == 0 ? 28 : PS % 20 == 0 ? 20 : 12;
+}
+template <typename T, int CW>
+struct WeightChunk {
+    T v[CW];
+};
+template <typename T, int CW>
+__device__ __forceinline__ WeightChunk<T, CW> load_chunk(const T *w) {
+    WeightChunk<T, CW> c;
+    const auto *p = (const __attribute__((address_space(4))) T *)w;
+#pragma unroll
+    for (int i = 0; i < CW; ++i) c.v[i] = p[i];
+    return c;
+}
+// a wavefront-uniform pointer, in scalar registers
+template <typename T>
+__device__ __forceinline__ const T *uniform_ptr(const T *p) {
+    const unsigned long long a = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    return (const T *)(((unsigned long long)hi << 32) | lo);
+}
+template <int... I, typename F>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F &&f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// cells_step with the weights of the step at w (global memory, wavefront-uniform) through scalar
+// registers; `cur` holds the first chunk of the step and, on return, that of the next
+template <typename T, int N, int SPLIT, int CW>
+__device__ __forceinline__ void cells_step_scalar(const typename cplx<T>::t (&mv)[N], const typename cplx<T>::t (&jv)[N],
+                                                  const T *w, WeightChunk<T, CW> &cur, T (&pr)[N], T (&pi)[N]) {
+    constexpr int h = N / 2;
+    WeightChunk<T, CW> nxt;
+    static_for(std::make_integer_sequence<int, N>{}, [&](auto K) {
+        constexpr int k3 = K;
+        constexpr int mlo = k3 - h + 1 > 0 ? k3 - h + 1 : 0;
+        constexpr int mhi = k3 + h < N - 1 ? k3 + h : N - 1;
+        T sr[SPLIT], si[SPLIT];
+#pragma unroll
+        for (int a = 0; a < SPLIT; ++a) sr[a] = si[a] = 0;
+        static_for(std::make_integer_sequence<int, mhi - mlo + 1>{}, [&](auto I) {
+            constexpr int m3 = mlo + I, j3 = k3 - m3 + h, a = I % SPLIT, t = step_koff(N, k3) + I;
+            if constexpr (t % CW == 0) {
+                if (t > 0) cur = nxt;
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the current chunk is here
+                nxt = load_chunk<T, CW>(w + t + CW);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const T wt = cur.v[t % CW];
+            const T px = fma(mv[m3].x, jv[j3].x, -(mv[m3].y * jv[j3].y));
+            const T py = fma(mv[m3].x, jv[j3].y, mv[m3].y * jv[j3].x);
+            sr[a] = fma(wt, px, sr[a]);
+            si[a] = fma(wt, py, si[a]);
+        });
+#pragma unroll
+        for (int st = 1; st < SPLIT; st *= 2)
+#pragma unroll
+            for (int a = 0; a + st < SPLIT; a += 2 * st) {
+                sr[a] += sr[a + st];
+                si[a] += si[a + st];
+            }
+        pr[k3] += sr[0];
+        pi[k3] += si[0];
+    });
+    cur = nxt;
 }
 
 template <typename T, int N>
@@ -186,6 +267,7 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
         return;
     }
     const float *w = (const float *)cp.w + cp.row_woff[r] + (long long)s0 * PS;
+    if constexpr (WP == 3) w = uniform_ptr(w);
     const float2 *G = fh + cp.fh_off + (size_t)g * M * kWave;   // this group's fhat (copy of the pass)
     const float2 *F = G + lane;
     const lds_float *const rbuf = (const lds_float *)rl;   // rows as (re, im) float pairs
@@ -236,9 +318,12 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
     int m1, m2;
     seek_step<N>(k1, k2, s0, m1, m2);
     const int lo2 = axis_lo(N, k2);
-    prefetch_weights<CH>(w, wl);
+    constexpr int CW = weight_chunk<float, N>();
+    WeightChunk<float, CW> wc;
+    if constexpr (WP == 3) wc = load_chunk<float, CW>(w);
+    else prefetch_weights<CH>(w, wl);
     if (RP && s0 < s1) prefetch_rows(m1, m2);
-    __builtin_amdgcn_s_waitcnt(0);
+    if (WP != 3) __builtin_amdgcn_s_waitcnt(0);
     int buf = 0, nst = 0;
     for (int s = s0; s < s1; ++s) {
         const int j1 = k1 + h - m1, j2 = k2 + h - m2;
@@ -268,6 +353,14 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
             // next step's weights into the other LDS half; this step reads its half
             prefetch_weights<CH>(w + PS, wl + (buf ^ 1) * CH * 1024);
             if (live) cells_step<float, N, SPLIT>(mv, jv, (const lds_float *)(wl + buf * CH * 1024), pr, pi);
+        } else if (WP == 3) {
+            // the next step's weights pulled into L2 (64 bytes a lane, the LDS copy is discarded)
+            constexpr int WL = (PS * 4 + 4095) / 4096;
+#pragma unroll
+            for (int c = 0; c < WL; ++c)
+                __builtin_amdgcn_global_load_lds((const void *)((const char *)(w + PS) + lane * 64 + c * 4096),
+                                                 (void __attribute__((address_space(3))) *)wl, 4, 0, 0);
+            cells_step_scalar<float, N, SPLIT, CW>(mv, jv, w, wc, pr, pi);
         } else if (WP == 1) {
             // next step's weights pulled into L2 (the LDS copy is discarded); this
             // step's weights, pulled last step, are read through the scalar cache
@@ -287,7 +380,7 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
         }
         m1 = n1;
         m2 = n2;
-        __builtin_amdgcn_s_waitcnt(0);
+        if (WP != 3) __builtin_amdgcn_s_waitcnt(0);
     }
     fold();
     if (COMP == 2) return;
@@ -438,10 +531,18 @@ k_conv_core(int N, int nD, const double2 *__restrict__ cf, const int4 *__restric
 // wavefronts per SIMD.  Items with kCoreItemBit are rows of an
 // FP64 core (core_item): spread through the queue, their row loads overlap the FP32
 // arithmetic of the other wavefront on the SIMD.
+// Weights by scalar loads from N = 28 on (N = 32, 190 cells: 3.9 against 4.2 ms a launch, whose
+// LDS broadcasts return 64 bytes a cycle and CU, less than the four SIMDs consume); below, where
+// a step is short (N = 16: 768 pairs), the wait for each chunk costs as much as the broadcasts
+// (72 to 521 cells within 1%, one N = 16 cell 2% slower).
+template <int N>
+constexpr int multi_weight_path() {
+    return N >= 28 ? 3 : 0;
+}
 template <int N>
 __device__ __forceinline__ void multi_item(const MeshConvDesc &d, char *ws, int pass, const int4 item, lds_char *wl) {
     const ConvPass cp = d.ps.p[pass];
-    cells_f32_item<N, 16, 2, 0, 0, 2>((const float2 *)(ws + d.fh_bytes), (double2 *)(ws + d.qh_bytes), nullptr, cp,
+    cells_f32_item<N, 16, 2, multi_weight_path<N>(), 0, 2>((const float2 *)(ws + d.fh_bytes), (double2 *)(ws + d.qh_bytes), nullptr, cp,
                                       item, wl, nullptr);
 }
 
