@@ -546,15 +546,136 @@ __device__ __forceinline__ void multi_item(const MeshConvDesc &d, char *ws, int 
                                       item, wl, nullptr);
 }
 
+// One FP32 item of a narrow group (NarrowTail: W = 2^lw cells).  The 64 lanes take W cells times
+// S = 64 / W consecutive steps of the row: lane l computes the per-output partials of step
+// s + l / W for cell l % W, with that step's weights, so the row's steps take 1/S as many
+// passes as with one cell on every lane and the other lanes idle (one
+// N=32 cell: 0.30 against 1.41 ms).  The partials go to LDS, half a row at a time, and are then added
+// to the running sums in step order, so the sums are bitwise those of a 64-cell group: a cell's
+// result does not depend on the width of its group.  The weights are read from memory once per
+// 16 bytes and lane (a step's weights are contiguous), kRing reads ahead of their use; that is
+// what bounds the pass: 16 cycles of the CU's L1 per 24 operations, as the broadcasts of LDS.
+// LDS: [N values][64 lanes] partials, [2N values][W cells] running sums (W <= 32), and 256 bytes
+// that the prefetches write.
+constexpr int kNarrowLdsBytes = 4 * kMaxN * (kWave + 2 * (kWave / 2));
+template <int N>
+__device__ __forceinline__ void narrow_item(const MeshConvDesc &d, char *ws, int pass, const int4 item, lds_char *lds) {
+    constexpr int h = N / 2, M = N * N * N, PS = 3 * N * N / 4, FOLD = 16, kRing = 14;
+    const ConvPass cp = d.ps.p[pass];
+    const int lw = d.tail_lw, W = 1 << lw, S = kWave >> lw;
+    const int lane = threadIdx.x, cell = lane & (W - 1), slice = lane >> lw;
+    const int g = item.x, r = item.y & 0xffff, part = (item.y >> 16) & 0xf, s0 = item.z, s1 = item.w;
+    const int k1 = r / N, k2 = r - k1 * N, lo2 = axis_lo(N, k2);
+    double *const out = (double *)((double2 *)(ws + d.qh_bytes) + cp.out_off + part * cp.pstride + g * cp.gstride) +
+                        ((size_t)(r - cp.row0) * N << (lw + 1));
+    lds_float *const part_l = (lds_float *)lds, *const run_l = part_l + N * kWave;
+    for (int i = lane; i < 2 * N * W; i += kWave) run_l[i] = 0.f;
+    if (s0 >= s1) {
+        for (int i = lane; i < 2 * N * W; i += kWave) out[i] = 0.0;
+        return;
+    }
+    const char *const wu = (const char *)uniform_ptr((const float *)cp.w + cp.row_woff[r] + (long long)s0 * PS);
+    const char *const G = (const char *)uniform_ptr((const float2 *)(ws + d.fh_bytes) + cp.fh_off + (size_t)g * M * kWave);
+    int m1, m2, at = slice < s1 - s0 ? s0 + slice : s1 - 1;   // this lane's step
+    seek_step<N>(k1, k2, at, m1, m2);
+    // weights of the pass at step s pulled into L2, one 128-byte line per lane and load (the copies
+    // in LDS are discarded): a pass reads its S steps' weights far faster than memory answers
+    // one line after the other
+    auto touch = [&](int s) {
+        const int bytes = (s1 - s < S ? s1 - s : S) * (PS * 4);
+        for (int o = lane * 128; o < bytes; o += kWave * 128)
+            __builtin_amdgcn_global_load_lds((const void *)(wu + (size_t)(s - s0) * (PS * 4) + o),
+                                             (void __attribute__((address_space(3))) *)(lds + kNarrowLdsBytes), 4, 0, 0);
+    };
+    touch(s0);
+    bool first = true;
+    for (int s = s0; s < s1; s += S) {
+        const int left = s1 - s < S ? s1 - s : S;             // steps of this pass
+        const bool fold = ((s + S - s0) % FOLD) == 0 || s + S >= s1;
+        const unsigned um = (unsigned)((((m1 * N + m2) * N) << lw) + cell) * 8u;
+        const unsigned uj = (unsigned)(((((k1 + h - m1) * N + (k2 + h - m2)) * N) << lw) + cell) * 8u;
+        const unsigned uw = (unsigned)(at - s0) * (PS * 4u);
+        float2 mv[N], jv[N];
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            mv[t] = *(const float2 *)(G + (t << (lw + 3)) + um);
+            jv[t] = *(const float2 *)(G + (t << (lw + 3)) + uj);
+        }
+        if (s + S < s1) touch(s + S);
+        float4 ring[kRing];
+#pragma unroll
+        for (int i = 0; i < kRing; ++i) ring[i] = *(const float4 *)(wu + uw + i * 16);
+        // the running sums of outputs k3 = K h .. K h + h - 1 from the partials in LDS
+        auto flush = [&](int half) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int i = lane; i < N * W; i += kWave) {
+                const int v = i >> lw, c = i & (W - 1), sw = (v << lw) & (kWave - 1), o = half * N * W + i;
+                float run = run_l[o];
+                for (int q = 0; q < left; ++q) run += part_l[v * kWave + (((q << lw) + c) ^ sw)];
+                if (fold) {
+                    // value v is component v % 2 of output k3 = half h + v / 2
+                    double *const p = out + (((size_t)(half * h + (v >> 1)) << lw) + c) * 2 + (v & 1);
+                    *p = (first ? 0.0 : *p) + (double)run;
+                    run = 0.f;
+                }
+                run_l[o] = run;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        static_for(std::make_integer_sequence<int, N>{}, [&](auto K) {
+            constexpr int k3 = K;
+            constexpr int mlo = k3 - h + 1 > 0 ? k3 - h + 1 : 0;
+            constexpr int mhi = k3 + h < N - 1 ? k3 + h : N - 1;
+            float sr[2] = {0.f, 0.f}, si[2] = {0.f, 0.f};
+            static_for(std::make_integer_sequence<int, mhi - mlo + 1>{}, [&](auto I) {
+                constexpr int m3 = mlo + I, j3 = k3 - m3 + h, a = I % 2, t = step_koff(N, k3) + I, c = t / 4;
+                const float4 q = ring[c % kRing];
+                const float wt = t % 4 == 0 ? q.x : t % 4 == 1 ? q.y : t % 4 == 2 ? q.z : q.w;
+                const float px = fma(mv[m3].x, jv[j3].x, -(mv[m3].y * jv[j3].y));
+                const float py = fma(mv[m3].x, jv[j3].y, mv[m3].y * jv[j3].x);
+                sr[a] = fma(wt, px, sr[a]);
+                si[a] = fma(wt, py, si[a]);
+                if constexpr (t % 4 == 3 && c + kRing < PS / 4)
+                    ring[c % kRing] = *(const float4 *)(wu + uw + (c + kRing) * 16);
+            });
+            // lane positions rotated by value, so that lanes reading different values hit different banks
+            constexpr int v = 2 * (k3 % h);
+            part_l[v * kWave + (lane ^ ((v << lw) & (kWave - 1)))] = sr[0] + sr[1];
+            part_l[(v + 1) * kWave + (lane ^ (((v + 1) << lw) & (kWave - 1)))] = si[0] + si[1];
+            if constexpr (k3 % h == h - 1) flush(k3 / h);
+        });
+        if (fold) first = false;
+        // this lane's next step
+        const int nx = at + S < s1 ? at + S : s1 - 1;
+        for (m2 += nx - at, at = nx;;) {
+            const int last = cells_m2_last(N, k1, k2, m1);
+            if (m2 <= last) break;
+            m2 -= last - lo2 + 1;
+            ++m1;
+        }
+    }
+}
+
+template <int N>
+__device__ __forceinline__ void fp32_item(const MeshConvDesc &d, char *ws, int pass, const int4 item, lds_char *lds) {
+    if (item.x == d.tail_g) narrow_item<N>(d, ws, pass, item, lds);
+    else multi_item<N>(d, ws, pass, item, lds);
+}
+
 template <int R>
 __device__ __forceinline__ void multi_core(const MeshConvDesc &d, char *ws, const int4 item, lds_char *wl) {
     core_item<R>(d.N, d.nD, (const double2 *)(ws + d.cf_bytes), d.core_steps, d.core_ext, d.core_w,
                  (double2 *)(ws + d.cq_bytes), d.cq_pstride, item, wl);
 }
 
-// LDS of the one-launch kernel: the largest FP32 step's weights (N = 32: 3 KiB) or the largest
-// core step's (r = 8: 17^2 doubles padded to 3 KiB), double-buffered
-constexpr int kMultiLdsBytes = 2 * 3 * 1024;
+// LDS of the one-launch kernel: the largest FP32 step's weights (N = 24: 2 KiB) or the largest
+// core step's (r = 8: 17^2 doubles padded to 3 KiB), double-buffered, or a narrow item's partials
+// and running sums (N = 32: 8 KiB and, for 32 cells, 8 KiB)
+constexpr int kMultiLdsBytes = kNarrowLdsBytes + 256;
 static_assert(2 * core_wstride(kCoreMaxR) * 8 <= kMultiLdsBytes, "core weights exceed the one-launch LDS buffer");
 
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
@@ -586,13 +707,13 @@ k_conv_cells_f32_multi(const int4 *__restrict__ items, int n_items, unsigned *__
             continue;
         }
         switch (d.N) {
-        case 8: multi_item<8>(d, ws, pass, item, wl); break;
-        case 12: multi_item<12>(d, ws, pass, item, wl); break;
-        case 16: multi_item<16>(d, ws, pass, item, wl); break;
-        case 20: multi_item<20>(d, ws, pass, item, wl); break;
-        case 24: multi_item<24>(d, ws, pass, item, wl); break;
-        case 28: multi_item<28>(d, ws, pass, item, wl); break;
-        default: multi_item<32>(d, ws, pass, item, wl); break;
+        case 8: fp32_item<8>(d, ws, pass, item, wl); break;
+        case 12: fp32_item<12>(d, ws, pass, item, wl); break;
+        case 16: fp32_item<16>(d, ws, pass, item, wl); break;
+        case 20: fp32_item<20>(d, ws, pass, item, wl); break;
+        case 24: fp32_item<24>(d, ws, pass, item, wl); break;
+        case 28: fp32_item<28>(d, ws, pass, item, wl); break;
+        default: fp32_item<32>(d, ws, pass, item, wl); break;
         }
     }
 }
@@ -811,8 +932,6 @@ hipError_t core_launch(const CoreLaunch &p, unsigned grid, hipStream_t s) {
 
 hipError_t launch_conv_cells_multi(const MultiLaunch &p, hipStream_t s) {
     if (p.n_items <= 0) return hipSuccess;
-    hipError_t e = launch_fill_u32(p.counter, 1, 0u, s);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_conv_cells_f32_multi, dim3(persistent_grid(p.n_items)), dim3(64), 0, s, p.items, p.n_items,
                        p.counter, p.desc, p.ws, p.skip);
     return hipGetLastError();

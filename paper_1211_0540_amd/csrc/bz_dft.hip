@@ -288,39 +288,60 @@ __device__ __forceinline__ void centred_dft(double2 (&x)[N]) {
     for (int k = 1; k < N; k += 2) x[k] = make_double2(-x[k].x, -x[k].y);
 }
 
-// line index of this wavefront (4 per block) and its lane
-#define BZ_LINE_SETUP                                         \
-    if (skip && skip[blockIdx.y]) return;                     \
-    constexpr int M = N * N * N;                              \
-    const int lane = threadIdx.x & (kWave - 1);               \
-    const int line = blockIdx.x * 4 + (threadIdx.x >> 6);     \
-    const int g = blockIdx.y;                                 \
-    const size_t gb = (size_t)g * M;                          \
-    (void)gb;
+// The work of one lane: its group, its cell's slot in the group and its line.  A group of 64 cells
+// puts one line on a wavefront (lane = cell); the narrow last group of a batch (NarrowTail) holds
+// W = 4 .. 32 cells, element (k, cell) at k W + cell, and puts 64 / W lines on a wavefront.
+template <bool NW>
+struct LaneOf {
+    int g, cell, line, lw;
+    bool live;
+    __device__ LaneOf(const NarrowTail &nt, int lines) {
+        const int lane = threadIdx.x & (kWave - 1);
+        const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+        g = blockIdx.y;
+        lw = NW ? nt.lw : 6;
+        cell = NW ? lane & ((1 << lw) - 1) : lane;
+        line = NW ? (wave << (6 - lw)) + (lane >> lw) : wave;
+        live = line < lines;
+    }
+    // offset of line element e of the group
+    __device__ size_t at(size_t e) const { return NW ? e << lw : e * kWave; }
+};
+
+// Calls body(LaneOf) for this lane of a grouped kernel (4 wavefronts per block, blockIdx.y = group).
+template <int N, typename F>
+__device__ __forceinline__ void grouped_lane(const NarrowTail &nt, const unsigned char *skip, F &&body) {
+    if (skip && skip[blockIdx.y]) return;
+    if ((int)blockIdx.y == nt.g) {
+        const LaneOf<true> l(nt, N * N);
+        if (l.live) body(l);
+    } else {
+        body(LaneOf<false>(nt, N * N));
+    }
+}
 
 // forward, axis 3: real f of cell g*64 + lane, line (j1, j2) -> S (j1, j2, k3)
 template <int N>
 __global__ void __launch_bounds__(256) k_dftg_fwd1(const double *__restrict__ f, const long long *__restrict__ f_off,
                                                    int nc, double2 *__restrict__ S,
-    const unsigned char *__restrict__ skip) {
-    BZ_LINE_SETUP
-    const int i = g * kWave + lane;
-    double x[N];
-    if (i < nc) {
-        const double *src = f + f_off[i] + (size_t)line * N;
+                                                   const unsigned char *__restrict__ skip, const NarrowTail nt) {
+    constexpr int M = N * N * N;
+    grouped_lane<N>(nt, skip, [&](const auto &l) {
+        const int i = l.g * kWave + l.cell;
+        double2 y[N];
+        if (i < nc) {
+            const double *src = f + f_off[i] + (size_t)l.line * N;
 #pragma unroll
-        for (int j = 0; j < N; ++j) x[j] = src[j];
-    } else {
+            for (int j = 0; j < N; ++j) y[j] = make_double2(src[j], 0.0);
+        } else {
 #pragma unroll
-        for (int j = 0; j < N; ++j) x[j] = 0.0;
-    }
-    double2 *dst = S + (gb + (size_t)line * N) * kWave + lane;
-    double2 y[N];
+            for (int j = 0; j < N; ++j) y[j] = make_double2(0.0, 0.0);
+        }
+        double2 *dst = S + (size_t)l.g * M * kWave + l.at((size_t)l.line * N) + l.cell;
+        centred_dft<N, -1>(y);
 #pragma unroll
-    for (int j = 0; j < N; ++j) y[j] = make_double2(x[j], 0.0);
-    centred_dft<N, -1>(y);
-#pragma unroll
-    for (int k = 0; k < N; ++k) dst[(size_t)k * kWave] = y[k];
+        for (int k = 0; k < N; ++k) dst[l.at(k)] = y[k];
+    });
 }
 
 // one complex line: out_k = scale sum_j in_j w^((k - N/2)(j - N/2)); out strided by `stride` elements
@@ -331,260 +352,281 @@ __device__ __forceinline__ void line_dft(double2 (&x)[N], double2 *dst, size_t s
     for (int k = 0; k < N; ++k) dst[k * stride] = make_double2(x[k].x * scale, x[k].y * scale);
 }
 
-// forward, axis 2: line (j1, k3): S (j1, j2, k3) -> T (j1, k2, k3)
-template <int N>
-__global__ void __launch_bounds__(256) k_dftg_fwd2(const double2 *__restrict__ S, double2 *__restrict__ T,
-    const unsigned char *__restrict__ skip) {
-    BZ_LINE_SETUP
-    const int j1 = line / N, k3 = line - j1 * N;
-    const size_t off = (gb + (size_t)j1 * N * N + k3) * kWave + lane;
-    double2 x[N];
+// axis 2, either direction: line (j1, k3): S (j1, a2, k3) -> T (j1, b2, k3)
+template <int N, int SIGN>
+__global__ void __launch_bounds__(256) k_dftg_mid(const double2 *__restrict__ S, double2 *__restrict__ T,
+                                                  const unsigned char *__restrict__ skip, const NarrowTail nt) {
+    constexpr int M = N * N * N;
+    grouped_lane<N>(nt, skip, [&](const auto &l) {
+        const int j1 = l.line / N, k3 = l.line - j1 * N;
+        const size_t off = (size_t)l.g * M * kWave + l.at((size_t)j1 * N * N + k3) + l.cell;
+        double2 x[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = S[off + (size_t)j * N * kWave];
-    line_dft<N, -1>(x, T + off, (size_t)N * kWave, 1.0);
+        for (int j = 0; j < N; ++j) x[j] = S[off + l.at((size_t)j * N)];
+        line_dft<N, SIGN>(x, T + off, l.at(N), 1.0);
+    });
 }
 
 // forward, axis 1: line (k2, k3): T (j1, k2, k3) -> fhat (k1, k2, k3), scaled, in the kernel's precision;
 // with copies = 4 also fhat with the axes ordered (2, 1, 3) and (3, 1, 2), and fhat with every k_d = 0
 // plane set to zero (axes in order), copy_stride elements apart
-// With cf non-NULL it also writes the FP64 rows of the low-frequency core (CoreFill).
+// With cf non-NULL it also writes the FP64 rows of the low-frequency core (CoreFill), whose lines
+// hold 64 cells in every group.  It clears the work-queue counter of the convolution that follows.
 template <int N, typename Out>
 __global__ void __launch_bounds__(256) k_dftg_fwd3(const double2 *__restrict__ T, int nc, double scale,
                                                    Out *__restrict__ fh, int copies, long long copy_stride,
                                                    double2 *__restrict__ cf, const int *__restrict__ disk_idx,
-                                                   int nD, int cr, int cr2,
-    const unsigned char *__restrict__ skip) {
-    BZ_LINE_SETUP
-    const size_t off = (gb + (size_t)line) * kWave + lane;
-    double2 x[N];
+                                                   int nD, int cr, int cr2, const unsigned char *__restrict__ skip,
+                                                   const NarrowTail nt, unsigned *__restrict__ counter) {
+    constexpr int M = N * N * N;
+    if (counter && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *counter = 0;
+    grouped_lane<N>(nt, skip, [&](const auto &l) {
+        const int k2 = l.line / N, k3 = l.line - k2 * N;
+        const size_t gl = (size_t)l.g * M * kWave + l.cell, off = gl + l.at(l.line);
+        double2 x[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = T[off + (size_t)j * N * N * kWave];
-    const bool live = g * kWave + lane < nc;
-    centred_dft<N, -1>(x);
+        for (int j = 0; j < N; ++j) x[j] = T[off + l.at((size_t)j * N * N)];
+        const bool live = l.g * kWave + l.cell < nc;
+        centred_dft<N, -1>(x);
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        Out v;
-        v.x = live ? x[k].x * scale : 0.0;
-        v.y = live ? x[k].y * scale : 0.0;
-        fh[off + (size_t)k * N * N * kWave] = v;
-        if (copies > 1) {
-            const int k2 = line / N, k3 = line - k2 * N;
-            const size_t gl = gb * kWave + lane;
-            fh[copy_stride + gl + ((size_t)(k2 * N + k) * N + k3) * kWave] = v;
-            fh[2 * copy_stride + gl + ((size_t)(k3 * N + k) * N + k2) * kWave] = v;
-            Out z = v;
-            if (k == 0 || k2 == 0 || k3 == 0) z.x = z.y = 0.0;
-            fh[3 * copy_stride + off + (size_t)k * N * N * kWave] = z;
-        }
-    }
-    if (cf) {
-        constexpr int h = N / 2;
-        const int k2 = line / N, k3 = line - k2 * N, t = k3 - (h - cr);
-        if (t >= 0 && t <= 2 * cr) {
-            const int b2 = (k2 - h) * (k2 - h), c2 = (k3 - h) * (k3 - h);
-#pragma unroll
-            for (int k = 0; k < N; ++k) {
-                const int a2 = (k - h) * (k - h);
-                if (a2 + b2 > cr2) continue;   // row (k, k2) is not in the core disk
-                const int d = disk_idx[k * N + k2];
-                const bool in = live && a2 + b2 + c2 <= cr2;
-                cf[(((size_t)g * nD + d) * (2 * cr + 1) + t) * kWave + lane] =
-                    in ? make_double2(x[k].x * scale, x[k].y * scale) : make_double2(0.0, 0.0);
+        for (int k = 0; k < N; ++k) {
+            Out v;
+            v.x = live ? x[k].x * scale : 0.0;
+            v.y = live ? x[k].y * scale : 0.0;
+            fh[off + l.at((size_t)k * N * N)] = v;
+            if (copies > 1) {
+                fh[copy_stride + gl + l.at((size_t)(k2 * N + k) * N + k3)] = v;
+                fh[2 * copy_stride + gl + l.at((size_t)(k3 * N + k) * N + k2)] = v;
+                Out z = v;
+                if (k == 0 || k2 == 0 || k3 == 0) z.x = z.y = 0.0;
+                fh[3 * copy_stride + off + l.at((size_t)k * N * N)] = z;
             }
         }
+        if (cf) {
+            constexpr int h = N / 2;
+            const int t = k3 - (h - cr);
+            if (t >= 0 && t <= 2 * cr) {
+                const int b2 = (k2 - h) * (k2 - h), c2 = (k3 - h) * (k3 - h);
+#pragma unroll
+                for (int k = 0; k < N; ++k) {
+                    const int a2 = (k - h) * (k - h);
+                    if (a2 + b2 > cr2) continue;   // row (k, k2) is not in the core disk
+                    const int d = disk_idx[k * N + k2];
+                    const bool in = live && a2 + b2 + c2 <= cr2;
+                    cf[(((size_t)l.g * nD + d) * (2 * cr + 1) + t) * kWave + l.cell] =
+                        in ? make_double2(x[k].x * scale, x[k].y * scale) : make_double2(0.0, 0.0);
+                }
+            }
+        }
+    });
+}
+
+// ---------------------------------------------------------------------------
+// Inverse, axis 1: Qhat(k1, k2, k3) of line (k2, k3) from the buffers of the convolution, then the
+// transform -> S (j1, k2, k3).  The line is assembled kAsm outputs at a time, the loads of one
+// buffer for all of them issued together: a load per output and buffer after the other left the
+// pass waiting for memory (N = 16, one group with 8 partial buffers: 57 us), all N outputs of a
+// line at once do not fit the registers.
+// ---------------------------------------------------------------------------
+constexpr int kAsm = 4;
+
+// The FP64 core sum (CoreAdd; core NULL when off) of outputs k1 = K0 .. K0 + kAsm - 1, added to every
+// output within 2cr of the centre.  The core holds it for the direct rows and for k3 = 0 of the derived
+// rows; elsewhere a derived output is the conjugate of its mirror N - k (the core pairs are
+// interior, and the weights even).  gl: the lane's element 0 of the group's core lines.
+template <int N, int K0>
+__device__ __forceinline__ void add_core(double2 (&x)[N], const CoreAdd &ca, size_t gl, int k2, int k3) {
+    constexpr int h = N / 2;
+    const int cr = ca.r;
+    double2 c[kAsm];
+    size_t o[kAsm];
+    bool in[kAsm], mirrored[kAsm];
+#pragma unroll
+    for (int i = 0; i < kAsm; ++i) {
+        const int k1 = K0 + i;
+        in[i] = abs(k1 - h) <= 2 * cr;
+        mirrored[i] = herm_derived_row(N, k1, k2) && k3 >= 1;
+        o[i] = gl + (size_t)(mirrored[i] ? ((N - k1) * N + (N - k2)) * N + (N - k3) : (k1 * N + k2) * N + k3) * kWave;
+        c[i] = in[i] ? ca.core[o[i]] : make_double2(0.0, 0.0);
+    }
+    // the partial sums of the row's step pieces, in piece order
+    for (int p = 1; p < ca.parts; ++p)
+#pragma unroll
+        for (int i = 0; i < kAsm; ++i)
+            if (in[i]) {
+                const double2 t = ca.core[o[i] + (size_t)p * ca.pstride];
+                c[i].x += t.x;
+                c[i].y += t.y;
+            }
+#pragma unroll
+    for (int i = 0; i < kAsm; ++i) {
+        if (!in[i]) continue;
+        x[K0 + i].x += c[i].x;
+        x[K0 + i].y += mirrored[i] ? -c[i].y : c[i].y;
     }
 }
 
-// inverse, axis 1, conjugate-symmetric schedule: assemble Qhat(k1, k2, k3) of line (k2, k3) from the
-// passes (qh: nA partial buffers of pass A, then the half-size E1, E2, E3, then nA partial buffers
-// of Z, laid out as HermAssembly describes; pstride = one full buffer), then transform -> S (j1, k2, k3).  Pass A holds the interior sums I of the direct rows.
+// outputs K0 .. K0 + kAsm - 1 of the conjugate-symmetric schedule (qh: nA partial buffers of pass A,
+// then the half-size E1, E2, E3, then nA partial buffers of Z, laid out as HermAssembly describes;
+// pstride = one full buffer).  Pass A holds the interior sums I of the direct rows.
 //   direct row (k1, k2):        Qhat = I(k) + E(k)
 //   derived row, k3 = 0:        Qhat = Z at (0, k1, k2) of the (3, 1, 2) order
 //   derived row, k3 >= 1:       Qhat = conj I(k') + E(k),   k' = N - k
 // E(k) is the edge sum: E1 at (k1, k2, k3) if k1 < N/2, E2 at (k2, k1, k3) if k2 < N/2,
 // E3 at (k3, k1, k2) if k3 < N/2.
-// Three wavefronts per SIMD: at N=32 that costs some register spills, but the 3 x 1024 lines of a
-// 190-cell batch then run in one round (139 instead of 157 us measured).
-// The FP64 core sum (CoreAdd; core NULL when off) is added to every output within 2cr of the centre.
-// The core holds it for the direct rows and for k3 = 0 of the derived rows; elsewhere a derived
-// output is the conjugate of its mirror N - k (the core pairs are interior, and the weights even).
-template <int N>
-__device__ __forceinline__ void add_core(double2 (&x)[N], const CoreAdd &ca, size_t gl, int k2, int k3) {
-    constexpr int h = N / 2;
-    const int cr = ca.r;
-    if (!ca.core || abs(k2 - h) > 2 * cr || abs(k3 - h) > 2 * cr) return;
-#pragma unroll
-    for (int k1 = 0; k1 < N; ++k1) {
-        if (abs(k1 - h) > 2 * cr) continue;
-        const bool mirrored = herm_derived_row(N, k1, k2) && k3 >= 1;
-        const size_t o = mirrored ? gl + ((size_t)((N - k1) * N + (N - k2)) * N + (N - k3)) * kWave
-                                  : gl + ((size_t)(k1 * N + k2) * N + k3) * kWave;
-        // the partial sums of the row's step pieces, in piece order
-        double2 c = ca.core[o];
-        for (int p = 1; p < ca.parts; ++p) {
-            const double2 t = ca.core[o + (size_t)p * ca.pstride];
-            c.x += t.x;
-            c.y += t.y;
-        }
-        if (mirrored) c.y = -c.y;
-        x[k1].x += c.x;
-        x[k1].y += c.y;
-    }
-}
-
-template <int N>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_dftg_inv1_herm(const double2 *__restrict__ qh, int nA, long long pstride,
-                                                        const CoreAdd core,
-                                                        double2 *__restrict__ S,
-    const unsigned char *__restrict__ skip) {
-    BZ_LINE_SETUP
-    constexpr int h = N / 2;
-    const int k2 = line / N, k3 = line - k2 * N;
-    // pstride = B, one full buffer; group bases of the full, edge (half) and Z buffers
-    const size_t gl = gb * kWave + lane;
-    const size_t ge = (size_t)g * (M / 2) * kWave + lane;
-    const size_t gz = (size_t)g * h * N * kWave + lane;
-    const double2 *E1 = qh + (size_t)nA * pstride;
-    const double2 *E2 = E1 + pstride / 2, *E3 = E2 + pstride / 2, *Z = E3 + pstride / 2;
+template <int N, int K0, typename L>
+__device__ __forceinline__ void assemble_herm(double2 (&x)[N], const double2 *__restrict__ qh, int nA,
+                                              long long pstride, const L &l, int k2, int k3) {
+    constexpr int h = N / 2, M = N * N * N;
+    // group bases of the full, edge (half) and Z buffers
+    const size_t gl = (size_t)l.g * M * kWave + l.cell;
+    const double2 *const E1 = qh + (size_t)nA * pstride + (size_t)l.g * (M / 2) * kWave + l.cell;
+    const double2 *const E2 = E1 + pstride / 2, *const E3 = E2 + pstride / 2;
+    const size_t z0 = (size_t)nA * pstride + 3 * (size_t)(pstride / 2) + (size_t)l.g * h * N * kWave + l.cell;
     const size_t zstride = (size_t)pstride / (2 * N);
-    auto at = [](int a, int b, int c) { return ((size_t)(a * N + b) * N + c) * kWave; };
-    auto sum_parts = [&](const double2 *base, size_t o, size_t stride) {
-        double2 a = base[o];
-        for (int p = 1; p < nA; ++p) {
-            const double2 b = base[o + (size_t)p * stride];
-            a.x += b.x;
-            a.y += b.y;
-        }
-        return a;
-    };
-    auto edge = [&](int a, int b, int c) {
-        double2 e = make_double2(0.0, 0.0);
-        if (a < h) {
-            const double2 t = E1[ge + at(a, b, c)];
-            e.x += t.x;
-            e.y += t.y;
-        }
-        if (b < h) {
-            const double2 t = E2[ge + at(b, a, c)];
-            e.x += t.x;
-            e.y += t.y;
-        }
-        if (c < h) {
-            const double2 t = E3[ge + at(c, a, b)];
-            e.x += t.x;
-            e.y += t.y;
-        }
-        return e;
-    };
-    double2 x[N];
+    size_t o[kAsm], st[kAsm];
+    bool derived[kAsm], z[kAsm];
+    double2 a[kAsm];
 #pragma unroll
-    for (int k1 = 0; k1 < N; ++k1) {
-        if (!herm_derived_row(N, k1, k2)) {
-            const double2 i = sum_parts(qh, gl + at(k1, k2, k3), pstride), e = edge(k1, k2, k3);
-            x[k1] = make_double2(i.x + e.x, i.y + e.y);
-        } else if (k3 == 0) {
-            // derived rows have k1 >= N/2: Z slot (k1 - N/2, k2) of the k3 = 0 plane
-            x[k1] = sum_parts(Z, gz + ((size_t)(k1 - h) * N + k2) * kWave, zstride);
-        } else {
-            const double2 i = sum_parts(qh, gl + at(N - k1, N - k2, N - k3), pstride), e = edge(k1, k2, k3);
-            x[k1] = make_double2(i.x + e.x, e.y - i.y);
+    for (int i = 0; i < kAsm; ++i) {
+        const int k1 = K0 + i;
+        derived[i] = herm_derived_row(N, k1, k2);
+        z[i] = derived[i] && k3 == 0;
+        // derived rows have k1 >= N/2: Z slot (k1 - N/2, k2) of the k3 = 0 plane
+        o[i] = z[i] ? z0 + l.at((size_t)((k1 - h) * N + k2))
+                    : gl + l.at((size_t)(derived[i] ? ((N - k1) * N + N - k2) * N + N - k3 : (k1 * N + k2) * N + k3));
+        st[i] = z[i] ? zstride : (size_t)pstride;
+        a[i] = qh[o[i]];
+    }
+    for (int p = 1; p < nA; ++p) {
+        double2 b[kAsm];
+#pragma unroll
+        for (int i = 0; i < kAsm; ++i) b[i] = qh[o[i] + (size_t)p * st[i]];
+#pragma unroll
+        for (int i = 0; i < kAsm; ++i) {
+            a[i].x += b[i].x;
+            a[i].y += b[i].y;
         }
     }
-    add_core<N>(x, core, gl, k2, k3);
-    line_dft<N, +1>(x, S + gl + (size_t)line * kWave, (size_t)N * N * kWave, 1.0);
-}
-
-// inverse, axis 1: line (k2, k3): sum of the partial buffers (k1, k2, k3) -> S (j1, k2, k3)
-template <int N>
-__global__ void __launch_bounds__(256) k_dftg_inv1(const double2 *__restrict__ qh, int nparts, long long pstride,
-                                                   const CoreAdd core,
-                                                   double2 *__restrict__ S,
-    const unsigned char *__restrict__ skip) {
-    BZ_LINE_SETUP
-    const size_t off = (gb + (size_t)line) * kWave + lane;
-    const int k2 = line / N, k3 = line - k2 * N;
-    double2 x[N];
+    double2 e[kAsm];
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-        double2 a = qh[off + (size_t)j * N * N * kWave];
-        for (int p = 1; p < nparts; ++p) {
-            const double2 b = qh[off + (size_t)j * N * N * kWave + (size_t)p * pstride];
-            a.x += b.x;
-            a.y += b.y;
-        }
-        x[j] = a;
+    for (int i = 0; i < kAsm; ++i) e[i] = make_double2(0.0, 0.0);
+    auto edge = [&](const double2 *E, int i, int p, int q, int r) {
+        const double2 t = E[l.at((size_t)((p * N + q) * N + r))];
+        e[i].x += t.x;
+        e[i].y += t.y;
+    };
+#pragma unroll
+    for (int i = 0; i < kAsm; ++i)
+        if (K0 + i < h) edge(E1, i, K0 + i, k2, k3);
+    if (k2 < h) {
+#pragma unroll
+        for (int i = 0; i < kAsm; ++i) edge(E2, i, k2, K0 + i, k3);
     }
-    add_core<N>(x, core, gb * kWave + lane, k2, k3);
-    line_dft<N, +1>(x, S + off, (size_t)N * N * kWave, 1.0);
+    if (k3 < h) {
+#pragma unroll
+        for (int i = 0; i < kAsm; ++i) edge(E3, i, k3, K0 + i, k2);
+    }
+#pragma unroll
+    for (int i = 0; i < kAsm; ++i)
+        x[K0 + i] = z[i]          ? a[i]
+                    : derived[i] ? make_double2(a[i].x + e[i].x, e[i].y - a[i].y)
+                                 : make_double2(a[i].x + e[i].x, a[i].y + e[i].y);
 }
 
-// inverse, axis 2: line (j1, k3): S (j1, k2, k3) -> T (j1, j2, k3)
-template <int N>
-__global__ void __launch_bounds__(256) k_dftg_inv2(const double2 *__restrict__ S, double2 *__restrict__ T,
-    const unsigned char *__restrict__ skip) {
-    BZ_LINE_SETUP
-    const int j1 = line / N, k3 = line - j1 * N;
-    const size_t off = (gb + (size_t)j1 * N * N + k3) * kWave + lane;
-    double2 x[N];
+// outputs K0 .. K0 + kAsm - 1 of the full-sum schedule: the sum of the partial buffers
+template <int N, int K0, typename L>
+__device__ __forceinline__ void assemble_full(double2 (&x)[N], const double2 *__restrict__ qh, int nparts,
+                                              long long pstride, const L &l) {
+    const size_t off = (size_t)l.g * N * N * N * kWave + l.at(l.line) + l.cell;
 #pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = S[off + (size_t)j * N * kWave];
-    line_dft<N, +1>(x, T + off, (size_t)N * kWave, 1.0);
+    for (int i = 0; i < kAsm; ++i) x[K0 + i] = qh[off + l.at((size_t)(K0 + i) * N * N)];
+    for (int p = 1; p < nparts; ++p)
+#pragma unroll
+        for (int i = 0; i < kAsm; ++i) {
+            const double2 b = qh[off + l.at((size_t)(K0 + i) * N * N) + (size_t)p * pstride];
+            x[K0 + i].x += b.x;
+            x[K0 + i].y += b.y;
+        }
+}
+
+// Three wavefronts per SIMD: at N=32 that costs some register spills, but the 3 x 1024 lines of a
+// 190-cell batch then run in one round.
+template <int N, bool HERM>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+k_dftg_inv1(const double2 *__restrict__ qh, int nparts, long long pstride, const CoreAdd core,
+            double2 *__restrict__ S, const unsigned char *__restrict__ skip, const NarrowTail nt) {
+    constexpr int M = N * N * N, h = N / 2;
+    grouped_lane<N>(nt, skip, [&](const auto &l) {
+        const int k2 = l.line / N, k3 = l.line - k2 * N;
+        const bool cores = core.core && abs(k2 - h) <= 2 * core.r && abs(k3 - h) <= 2 * core.r;
+        double2 x[N];
+        [&]<int... C>(std::integer_sequence<int, C...>) {
+            ((void)[&] {
+                if constexpr (HERM) assemble_herm<N, kAsm * C>(x, qh, nparts, pstride, l, k2, k3);
+                else assemble_full<N, kAsm * C>(x, qh, nparts, pstride, l);
+                if (cores) add_core<N, kAsm * C>(x, core, (size_t)l.g * M * kWave + l.cell, k2, k3);
+                __builtin_amdgcn_sched_barrier(0);
+            }(), ...);
+        }(std::make_integer_sequence<int, N / kAsm>{});
+        line_dft<N, +1>(x, S + (size_t)l.g * M * kWave + l.at(l.line) + l.cell, l.at((size_t)N * N), 1.0);
+    });
 }
 
 // inverse, axis 3: line (j1, j2): T (j1, j2, k3) -> Qt (j1, j2, j3) = scale Re(...) of cell g*64 + lane
 template <int N>
 __global__ void __launch_bounds__(256) k_dftg_inv3(const double2 *__restrict__ T, int nc, double scale,
                                                    double *__restrict__ qt, const long long *__restrict__ q_off,
-    const unsigned char *__restrict__ skip) {
-    BZ_LINE_SETUP
-    const int i = g * kWave + lane;
-    const size_t off = (gb + (size_t)line * N) * kWave + lane;
-    double2 x[N];
+                                                   const unsigned char *__restrict__ skip, const NarrowTail nt) {
+    constexpr int M = N * N * N;
+    grouped_lane<N>(nt, skip, [&](const auto &l) {
+        const int i = l.g * kWave + l.cell;
+        const size_t off = (size_t)l.g * M * kWave + l.at((size_t)l.line * N) + l.cell;
+        double2 x[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = T[off + (size_t)j * kWave];
-    if (i >= nc) return;
-    double *dst = qt + q_off[i] + (size_t)line * N;
-    centred_dft<N, +1>(x);
+        for (int j = 0; j < N; ++j) x[j] = T[off + l.at(j)];
+        if (i >= nc) return;
+        double *dst = qt + q_off[i] + (size_t)l.line * N;
+        centred_dft<N, +1>(x);
 #pragma unroll
-    for (int k = 0; k < N; ++k) dst[k] = x[k].x * scale;
+        for (int k = 0; k < N; ++k) dst[k] = x[k].x * scale;
+    });
 }
-#undef BZ_LINE_SETUP
 
 template <int N>
 hipError_t grouped_forward(double L, int nc, const double *f, const long long *f_off, double2 *S, double2 *T,
                            void *fh, bool f32, int copies, const CoreFill &cfill, const unsigned char *skip,
-                           hipStream_t s) {
+                           const NarrowTail &nt, unsigned *counter, hipStream_t s) {
     const int groups = (nc + kWave - 1) / kWave;
     const dim3 grid(N * N / 4, groups);
     const double dv = 2.0 * L / N;
     const double scale = pow(2.0 * kPi, -1.5) * dv * dv * dv;
     const long long cstride = (long long)groups * N * N * N * kWave;
-    hipLaunchKernelGGL(k_dftg_fwd1<N>, grid, dim3(256), 0, s, f, f_off, nc, S, skip);
-    hipLaunchKernelGGL(k_dftg_fwd2<N>, grid, dim3(256), 0, s, S, T, skip);
+    hipLaunchKernelGGL(k_dftg_fwd1<N>, grid, dim3(256), 0, s, f, f_off, nc, S, skip, nt);
+    hipLaunchKernelGGL((k_dftg_mid<N, -1>), grid, dim3(256), 0, s, S, T, skip, nt);
     if (f32)
         hipLaunchKernelGGL((k_dftg_fwd3<N, float2>), grid, dim3(256), 0, s, T, nc, scale, (float2 *)fh, copies,
-                           cstride, cfill.cf, cfill.disk_idx, cfill.nD, cfill.r, cfill.r2, skip);
+                           cstride, cfill.cf, cfill.disk_idx, cfill.nD, cfill.r, cfill.r2, skip, nt, counter);
     else
         hipLaunchKernelGGL((k_dftg_fwd3<N, double2>), grid, dim3(256), 0, s, T, nc, scale, (double2 *)fh, copies,
-                           cstride, cfill.cf, cfill.disk_idx, cfill.nD, cfill.r, cfill.r2, skip);
+                           cstride, cfill.cf, cfill.disk_idx, cfill.nD, cfill.r, cfill.r2, skip, nt, counter);
     return hipGetLastError();
 }
 
 template <int N>
 hipError_t grouped_inverse(double L, int nc, const double2 *qh, int nparts, long long pstride,
                            const HermAssembly &herm, const CoreAdd &core, double2 *S, double2 *T, double *qt,
-                           const long long *q_off, const unsigned char *skip, hipStream_t s) {
+                           const long long *q_off, const unsigned char *skip, const NarrowTail &nt, hipStream_t s) {
     const int groups = (nc + kWave - 1) / kWave;
     const dim3 grid(N * N / 4, groups);
     const double dz = kPi / L;
     const double scale = pow(2.0 * kPi, -1.5) * dz * dz * dz;
     if (herm.on)
-        hipLaunchKernelGGL(k_dftg_inv1_herm<N>, grid, dim3(256), 0, s, qh, herm.nA, pstride, core, S,
-                           skip);
+        hipLaunchKernelGGL((k_dftg_inv1<N, true>), grid, dim3(256), 0, s, qh, herm.nA, pstride, core, S, skip, nt);
     else
-        hipLaunchKernelGGL(k_dftg_inv1<N>, grid, dim3(256), 0, s, qh, nparts, pstride, core, S, skip);
-    hipLaunchKernelGGL(k_dftg_inv2<N>, grid, dim3(256), 0, s, S, T, skip);
-    hipLaunchKernelGGL(k_dftg_inv3<N>, grid, dim3(256), 0, s, T, nc, scale, qt, q_off, skip);
+        hipLaunchKernelGGL((k_dftg_inv1<N, false>), grid, dim3(256), 0, s, qh, nparts, pstride, core, S, skip, nt);
+    hipLaunchKernelGGL((k_dftg_mid<N, +1>), grid, dim3(256), 0, s, S, T, skip, nt);
+    hipLaunchKernelGGL(k_dftg_inv3<N>, grid, dim3(256), 0, s, T, nc, scale, qt, q_off, skip, nt);
     return hipGetLastError();
 }
 
@@ -594,11 +636,12 @@ hipError_t grouped_inverse(double L, int nc, const double2 *qh, int nparts, long
 
 hipError_t launch_dft_forward_grouped(int N, double L, int ncells, const double *f, const long long *d_f_off,
                                       double2 *S, double2 *T, void *fh, bool out_f32, int copies,
-                                      const CoreFill &core, const unsigned char *skip, hipStream_t s) {
+                                      const CoreFill &core, const unsigned char *skip, const NarrowTail &nt,
+                                      unsigned *counter, hipStream_t s) {
     if (ncells <= 0) return hipSuccess;
     if (copies != 1 && copies != 4) return hipErrorInvalidValue;
 #define CASE(NN) \
-    case NN: return grouped_forward<NN>(L, ncells, f, d_f_off, S, T, fh, out_f32, copies, core, skip, s);
+    case NN: return grouped_forward<NN>(L, ncells, f, d_f_off, S, T, fh, out_f32, copies, core, skip, nt, counter, s);
     switch (N) {
         BZ_FOR_EACH_N(CASE)
     default:
@@ -610,10 +653,10 @@ hipError_t launch_dft_forward_grouped(int N, double L, int ncells, const double 
 hipError_t launch_dft_inverse_grouped(int N, double L, int ncells, const double2 *qh, int nparts, long long pstride,
                                       const HermAssembly &herm, const CoreAdd &core, double2 *S, double2 *T,
                                       double *qt, const long long *d_q_off, const unsigned char *skip,
-                                      hipStream_t s) {
+                                      const NarrowTail &nt, hipStream_t s) {
     if (ncells <= 0) return hipSuccess;
 #define CASE(NN) \
-    case NN: return grouped_inverse<NN>(L, ncells, qh, nparts, pstride, herm, core, S, T, qt, d_q_off, skip, s);
+    case NN: return grouped_inverse<NN>(L, ncells, qh, nparts, pstride, herm, core, S, T, qt, d_q_off, skip, nt, s);
     switch (N) {
         BZ_FOR_EACH_N(CASE)
     default:

@@ -311,13 +311,21 @@ struct CoreFill {
     const int *disk_idx;   // device, N*N
     int nD, r, r2;
 };
+// The last group of a mesh's cells, when it holds at most half of 64 and runs in the narrow layout:
+// W = 2^lw cells (4 to 32), element (k, cell) of its buffers at k W + cell from the group's base;
+// g = -1: none.  The core lines keep 64 cells.
+struct NarrowTail {
+    int g, lw;
+};
+// counter (may be NULL): cleared by the last forward pass
 hipError_t launch_dft_forward_grouped(int N, double L, int ncells, const double *f, const long long *d_f_off,
                                       double2 *S, double2 *T, void *fh, bool out_f32, int copies,
-                                      const CoreFill &core, const unsigned char *skip, hipStream_t s);
+                                      const CoreFill &core, const unsigned char *skip, const NarrowTail &nt,
+                                      unsigned *counter, hipStream_t s);
 hipError_t launch_dft_inverse_grouped(int N, double L, int ncells, const double2 *qh, int nparts, long long pstride,
                                       const HermAssembly &herm, const CoreAdd &core, double2 *S, double2 *T,
                                       double *qt, const long long *d_q_off, const unsigned char *skip,
-                                      hipStream_t s);
+                                      const NarrowTail &nt, hipStream_t s);
 hipError_t launch_dft_forward(int N, double L, int ncells, const double *f, const long long *d_f_off,
                               double2 *scratch, void *out, bool out_f32, const long long *d_o_base,
                               long long o_stride, hipStream_t s);
@@ -376,6 +384,7 @@ struct MeshConvDesc {
     const int *core_ext;         // per disk row: its half-width in m3 inside the ball
     const double *core_w;
     int nD, core_r;
+    int tail_g, tail_lw;         // narrow last group (NarrowTail), -1: none
 };
 // bit 28 of an item's row word marks an FP64 core item in the one-launch queue
 constexpr int kCoreItemBit = 1 << 28;
@@ -384,7 +393,7 @@ constexpr int kCoreMaxParts = 4;
 struct MultiLaunch {
     const int4 *items;
     int n_items;
-    unsigned *counter;
+    unsigned *counter;           // device, zero (cleared by the forward transforms)
     const MeshConvDesc *desc;    // device
     char *ws;                    // the call's workspace
     const unsigned char *skip;   // device, per group (one-mesh batches), may be NULL: groups to leave out

@@ -397,6 +397,7 @@ struct Part {
     int gi = 0;
     std::vector<int> cells;  // batch cell indices
     int groups = 0;
+    NarrowTail tail{-1, 6};          // the last group's layout in the one-launch form
     const void *w = nullptr;
     int wkind = 0;
     // device tables (offsets into the batch's device buffer)
@@ -764,6 +765,16 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
             if (grid_of_cell[c] == gi) p.cells.push_back(c);
         if (p.cells.empty()) continue;
         p.groups = (int)((p.cells.size() + kWave - 1) / kWave);
+        // a last group of at most 32 cells: W = 4, 8, 16 or 32 lanes hold its cells in the one launch,
+        // which takes 64 / W steps of a row at once (FP32 items of one group, W = 64 / 32 / 4: N = 32
+        // 1.41 / 1.24 / 0.30 ms, N = 24 345 / 286 / 104 us, N = 16 80 / 74 / 44 us; above 32 cells
+        // there is no second step to take)
+        const int rest = (int)(p.cells.size() % kWave);
+        if (rest >= 1 && rest <= kWave / 2) {
+            p.tail.g = p.groups - 1;
+            p.tail.lw = 2;
+            while ((1 << p.tail.lw) < rest) ++p.tail.lw;
+        }
         // untuned default: the output-slot variant with interleaved partials from N = 24 on,
         // the in-register FP64 total with interleaved partials below (measured on MI355X)
         p.variant = recalled_variant(tune_key(p.g->N, p.groups, mode), p.g->N >= 24 ? 10 : 13);
@@ -951,8 +962,10 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
             }
         }
         auto cost = [&](const int4 &x) {
-            const int N = b->parts[(x.y >> 24) & 0xf].g->N;
-            return (long long)(x.w - x.z) * pairs_per_step(N);
+            const Part &p = b->parts[(x.y >> 24) & 0xf];
+            // a narrow group takes kWave / W steps at once
+            const int S = x.x == p.tail.g ? kWave >> p.tail.lw : 1;
+            return (long long)((x.w - x.z + S - 1) / S) * pairs_per_step(p.g->N);
         };
         std::stable_sort(conv.begin(), conv.end(), [&](const int4 &x, const int4 &y) { return cost(x) > cost(y); });
         std::stable_sort(core.begin(), core.end(), [](const int4 &x, const int4 &y) { return x.w - x.z > y.w - y.z; });
@@ -1084,6 +1097,8 @@ bz_status bz_batch_set_weights(bz_batch b, int grid_index, int kind, const void 
             d[i].qh_bytes = (long long)p.ws_qh;
             d[i].N = p.g->N;
             d[i].ps = conv_passes(p, false);
+            d[i].tail_g = p.tail.g;
+            d[i].tail_lw = p.tail.lw;
             if (p.core) {
                 const CoreSched &cs = p.g->sched.core;
                 d[i].cf_bytes = (long long)p.ws_cf;
@@ -1392,7 +1407,8 @@ static bz_status collide_batched(bz_batch b, const double *d_f, double *d_Qt, ch
         const CoreFill cfill{p.core ? (double2 *)(ws + p.ws_cf) : nullptr, p.d_disk_idx, cs.nD, cs.r, cs.r2};
         BZ_HIP(launch_dft_forward_grouped(p.g->N, p.g->L, (int)p.cells.size(), d_f, f_off, scratch,
                                           (double2 *)(ws + p.ws_qh), ws + p.ws_fh, !f64, p.herm ? 4 : 1, cfill, skip,
-                                          s),
+                                          merged ? p.tail : NarrowTail{-1, 6},
+                                          merged ? (unsigned *)(ws + b->ws_mcounter) : nullptr, s),
                "forward transform");
     }
     // the FP64 cores: in the one-launch queue, or else on their own stream after the forward
@@ -1454,7 +1470,7 @@ static bz_status collide_batched(bz_batch b, const double *d_f, double *d_Qt, ch
         // groups whose cells are all served by the closure (skip) need no transforms: the
         // closure writes their outputs
         BZ_HIP(launch_dft_inverse_grouped(p.g->N, p.g->L, (int)p.cells.size(), qh, p.parts, pstride, herm, cadd,
-                                          scratch, qh, d_Qt, f_off, skip, s),
+                                          scratch, qh, d_Qt, f_off, skip, merged ? p.tail : NarrowTail{-1, 6}, s),
                "inverse transform");
     }
     return BZ_OK;

@@ -1,0 +1,40 @@
+"""Narrow last groups of the one-launch convolution (at most 32 cells, W = 4, 8, 16 or 32 lanes of
+cells and 64 / W steps at once) against the same cells in 64-cell groups: the per-mesh launches
+with the same accumulation variant use the wide layout for every group.  The partial sums of a
+narrow item are added in step order, so the results are bitwise equal."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1211_0540_amd import bz
+from paper_1211_0540_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+_WCACHE = {}
+
+
+@pytest.fixture(scope="module")
+def dev():
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    return torch.device("cuda:0")
+
+
+# widths 4, 8, 16, 32 at their first and last cell counts, alone and after a full group, on every mesh
+@pytest.mark.parametrize("N,L,n,schedule", [
+    (8, 4.0, 1, "symmetric"), (8, 4.0, 96, "full"), (12, 5.0, 5, "symmetric"), (12, 5.0, 68, "full"),
+    (16, 6.0, 4, "symmetric"), (16, 6.0, 9, "full"), (20, 6.0, 8, "symmetric"), (20, 6.0, 81, "symmetric"),
+    (24, 7.0, 16, "full"), (24, 7.0, 72, "symmetric"), (28, 7.0, 17, "symmetric"), (28, 7.0, 1, "full"),
+    (32, 8.0, 32, "symmetric"), (32, 8.0, 3, "symmetric"), (32, 8.0, 33, "symmetric")])
+def test_narrow_groups_are_bitwise_the_wide_ones(dev, N, L, n, schedule):
+    cells = list(W.random_smooth_cells(n, N, L, seed=300 + N, umax=0.5))
+    out = []
+    for per_mesh in (False, True):
+        c = bz.Collision([(N, L, 1.0)], [0] * n, "batched_f32", weights_cache=_WCACHE, schedule=schedule,
+                         per_mesh=per_mesh)
+        assert bz.bz_batch_one_launch(c.batch) != per_mesh
+        c.set_variant(12)
+        f = torch.from_numpy(c.pack(cells)).to(dev)
+        out.append(c.collide(f).cpu().numpy())
+        c.close()
+    assert np.all(np.isfinite(out[0]))
+    assert np.array_equal(out[0], out[1])
