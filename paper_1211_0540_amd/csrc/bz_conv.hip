@@ -419,7 +419,7 @@ k_conv_cells_f32(const float2 *__restrict__ fh, const int4 *__restrict__ items, 
 // the sum, so they are summed here in FP64 from FP64 fhat, with FP64 weights.
 // Lane = cell, like the batched kernels; an item is one output row of one
 // group.  A step loads its two rows (2R + 1 values each) and reads its
-// (2R + 1)^2 weights from LDS, copied there during the previous step.  Item
+// (2R + 1)^2 weights by scalar loads.  Item
 // kinds (bits 16..17 of the row word): 2 = every output of the row
 // (k3 - N/2 in [-2R, 2R]); 0 = only k3 - N/2 in [-2R, 0] (rows whose other
 // outputs follow from conjugate symmetry); 1 = only [1, 2R].  A full row
@@ -432,54 +432,77 @@ struct CoreOut {
     static constexpr int n = hi - lo + 1;
 };
 
-// am, aj: the half-widths of the two rows inside the ball (wavefront-uniform); entries beyond
-// them are zero, so they are neither loaded nor multiplied.
+// One core step: rows pm and pj of half-widths am and aj inside the ball (wavefront-uniform; entries
+// beyond them are zero), weights at w, through scalar registers like the FP32 items': the row of S
+// weights of the next m value is requested while the current one is used, and the m values are
+// loaded kAhead before their use.  (Weights from LDS, each read waited for between the branches of
+// its product, took 14 of the 18 us of a step: one N = 32 cell 915 us a launch, its FP32 items
+// 330.)  m values outside the ball are skipped, and j values kTj at a time.
 template <int R, int KIND>
-__device__ __forceinline__ void core_step(const double2 *pm, const double2 *pj, int am, int aj, const lds_double *wl,
+__device__ __forceinline__ void core_step(const double2 *pm, const double2 *pj, int am, int aj, const double *w,
                                           double2 (&acc)[CoreOut<R, KIND>::n]) {
-    constexpr int S = 2 * R + 1, LO = CoreOut<R, KIND>::lo, HI = CoreOut<R, KIND>::hi;
-    double2 jr[S];
+    constexpr int S = 2 * R + 1, LO = CoreOut<R, KIND>::lo, HI = CoreOut<R, KIND>::hi, kAhead = 3, kTj = 2;
+    double2 jr[S], mr[kAhead];
 #pragma unroll
-    for (int t = 0; t < S; ++t) jr[t] = abs(t - R) <= aj ? pj[t * kWave] : make_double2(0.0, 0.0);
+    for (int t = 0; t < kAhead; ++t) mr[t] = pm[t * kWave];
 #pragma unroll
-    for (int tm = 0; tm < S; ++tm) {
-        if (abs(tm - R) > am) continue;
-        const double2 mv = pm[tm * kWave];
-#pragma unroll
-        for (int tj = 0; tj < S; ++tj) {
-            const int e = tm + tj - 2 * R;   // k3 - N/2
-            if (e >= LO && e <= HI && abs(tj - R) <= aj) {
-                const double wt = wl[tm * S + tj];
-                const double px = fma(mv.x, jr[tj].x, -(mv.y * jr[tj].y));
-                const double py = fma(mv.x, jr[tj].y, mv.y * jr[tj].x);
-                acc[e - LO].x = fma(wt, px, acc[e - LO].x);
-                acc[e - LO].y = fma(wt, py, acc[e - LO].y);
-            }
+    for (int t = 0; t < S; ++t) jr[t] = pj[t * kWave];
+    WeightChunk<double, S> cur = load_chunk<double, S>(w), nxt;
+    static_for(std::make_integer_sequence<int, S>{}, [&](auto T) {
+        constexpr int tm = T;
+        const double2 mv = mr[tm % kAhead];
+        if constexpr (tm + kAhead < S) mr[tm % kAhead] = pm[(tm + kAhead) * kWave];
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+        if constexpr (tm + 1 < S) nxt = load_chunk<double, S>(w + (tm + 1) * S);
+        constexpr int dm = tm < R ? R - tm : tm - R;
+        if (dm <= am) {
+            // j values R - a and R + a
+            static_for(std::make_integer_sequence<int, (R + kTj) / kTj>{}, [&](auto B) {
+                constexpr int a0 = B * kTj;
+                if (a0 > aj) return;
+                static_for(std::make_integer_sequence<int, 2 * kTj>{}, [&](auto I) {
+                    constexpr int a = a0 + I / 2, tj = I % 2 ? R + a : R - a, e = tm + tj - 2 * R;   // k3 - N/2
+                    if constexpr (a <= R && (a > 0 || I % 2) && e >= LO && e <= HI) {
+                        const double wt = cur.v[tj];
+                        const double px = fma(mv.x, jr[tj].x, -(mv.y * jr[tj].y));
+                        const double py = fma(mv.x, jr[tj].y, mv.y * jr[tj].x);
+                        acc[e - LO].x = fma(wt, px, acc[e - LO].x);
+                        acc[e - LO].y = fma(wt, py, acc[e - LO].y);
+                    }
+                });
+            });
         }
-    }
+        cur = nxt;
+    });
 }
 
 template <int R, int KIND>
 __device__ __forceinline__ void core_rows(int N, const double2 *G, const int *steps, const int *ext, const double *ws,
-                                          int s0, int s1, double2 *o, lds_char *wl) {
-    constexpr int S = 2 * R + 1, WS = core_wstride(R), CH = WS * 8 / 1024;
+                                          int s0, int s1, double2 *o, lds_char *sink) {
+    constexpr int S = 2 * R + 1, WS = core_wstride(R), WL = (WS * 8 + 8191) / 8192;
     constexpr int LO = CoreOut<R, KIND>::lo, NO = CoreOut<R, KIND>::n;
-    const int h = N / 2;
+    const int h = N / 2, lane = threadIdx.x;
     double2 acc[NO];
 #pragma unroll
     for (int a = 0; a < NO; ++a) acc[a] = make_double2(0.0, 0.0);
-    if (s0 < s1) prefetch_weights<CH>(ws, wl);
-    __builtin_amdgcn_s_waitcnt(0);
-    int buf = 0;
+    const double *w = uniform_ptr(ws);
+    // a step's rows and their half-widths, read a step ahead
+    int st = s0 < s1 ? steps[s0] : 0, em = ext[st & 0xffff], ej = ext[st >> 16];
     for (int s = s0; s < s1; ++s) {
-        const int st = steps[s], dm = st & 0xffff, dj = st >> 16;
-        const double2 *pm = G + (size_t)dm * S * kWave;
-        const double2 *pj = G + (size_t)dj * S * kWave;
-        if (s + 1 < s1) prefetch_weights<CH>(ws + WS, wl + (buf ^ 1) * WS * 8);
-        core_step<R, KIND>(pm, pj, ext[dm], ext[dj], (const lds_double *)(wl + buf * WS * 8), acc);
-        ws += WS;
-        buf ^= 1;
-        __builtin_amdgcn_s_waitcnt(0);
+        const int dm = __builtin_amdgcn_readfirstlane(st) & 0xffff, dj = __builtin_amdgcn_readfirstlane(st) >> 16;
+        const int am = __builtin_amdgcn_readfirstlane(em), aj = __builtin_amdgcn_readfirstlane(ej);
+        const int sn = steps[s + 1 < s1 ? s + 1 : s];
+        // the next step's weights pulled into L2, a 128-byte line per lane (the copy in LDS is discarded)
+#pragma unroll
+        for (int c = 0; c < WL; ++c)
+            if (lane * 128 + c * 8192 < WS * 8)
+                __builtin_amdgcn_global_load_lds((const void *)((const char *)(w + WS) + lane * 128 + c * 8192),
+                                                 (void __attribute__((address_space(3))) *)sink, 4, 0, 0);
+        core_step<R, KIND>(G + (size_t)dm * S * kWave, G + (size_t)dj * S * kWave, am, aj, w, acc);
+        w += WS;
+        st = sn;
+        em = ext[sn & 0xffff];
+        ej = ext[sn >> 16];
     }
 #pragma unroll
     for (int a = 0; a < NO; ++a) {
@@ -506,14 +529,61 @@ __device__ __forceinline__ void core_item(int N, int nD, const double2 *cf, cons
     else core_rows<R, 1>(N, G, steps, ext, ws, s0, s1, o, wl);
 }
 
+// One core item of a narrow group of W = 2^lw cells, W <= 8: the outputs of the row are spread over the
+// lanes too.  With S = 2R + 1, lane l takes cell l % W and the residues rho = l / W, l / W + 64 / W, ...
+// below S; for a residue each m value meets one j value, tj = rho - tm (mod S), whose product goes to output
+// tm + tj = rho or rho + S.  A step is then S products and loads per residue, all independent, in place of
+// S^2 products one after the other (one N = 32 cell: 490 us a launch with the wide item, whose longest
+// row of 50 steps outlasted everything else by 200 us).  Each output takes its products in the
+// same order as in the wide item (those left out there are zero), so the sums are bitwise equal.
+template <int R>
+__device__ __forceinline__ void narrow_core_item(int N, int nD, const double2 *cf, const int *steps, const double *w,
+                                                 double2 *out, long long pstride, const int4 item, int lw) {
+    constexpr int S = 2 * R + 1, WS = core_wstride(R);
+    const int lane = threadIdx.x, cell = lane & ((1 << lw) - 1), h = N / 2;
+    const int g = item.x, row = item.y & 0xffff, kind = (item.y >> 16) & 3, piece = (item.y >> 20) & 0xf;
+    double2 *const o = out + (size_t)piece * pstride + ((size_t)g * N * N * N + (size_t)row * N) * kWave + cell;
+    const double2 *const G = cf + (size_t)g * nD * S * kWave + cell;
+    for (int rho = lane >> lw; rho < S; rho += kWave >> lw) {
+        double2 lo = make_double2(0.0, 0.0), hi = lo;
+        int st = item.z < item.w ? steps[item.z] : 0;
+        for (int s = item.z; s < item.w; ++s) {
+            const double2 *const pm = G + (size_t)(st & 0xffff) * S * kWave, *const pj = G + (size_t)(st >> 16) * S * kWave;
+            const double *const ws = w + (size_t)s * WS;
+            st = steps[s + 1 < item.w ? s + 1 : s];
+            double2 mv[S], jv[S];
+            double wt[S];
+#pragma unroll
+            for (int tm = 0; tm < S; ++tm) {
+                const int tj = rho - tm + (tm > rho ? S : 0);
+                mv[tm] = pm[tm * kWave];
+                jv[tm] = pj[tj * kWave];
+                wt[tm] = ws[tm * S + tj];
+            }
+#pragma unroll
+            for (int tm = 0; tm < S; ++tm) {
+                const double px = fma(mv[tm].x, jv[tm].x, -(mv[tm].y * jv[tm].y));
+                const double py = fma(mv[tm].x, jv[tm].y, mv[tm].y * jv[tm].x);
+                double2 &acc = tm > rho ? hi : lo;
+                acc.x = fma(wt[tm], px, acc.x);
+                acc.y = fma(wt[tm], py, acc.y);
+            }
+        }
+        // outputs k3 - N/2 = rho - 2R and rho - 2R + S, within the item's kind and the mesh
+        const int e0 = rho - 2 * R, e1 = e0 + S;
+        if (kind != 1 && h + e0 >= 0) o[(h + e0) * kWave] = lo;
+        if (rho < S - 1 && (e1 <= 0 ? kind != 1 : kind != 0) && h + e1 >= 0 && h + e1 < N) o[(h + e1) * kWave] = hi;
+    }
+}
+
 template <int R>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 k_conv_core(int N, int nD, const double2 *__restrict__ cf, const int4 *__restrict__ items, int n_items,
             unsigned *__restrict__ counter, const int *__restrict__ steps, const int *__restrict__ ext,
             const double *__restrict__ w, double2 *__restrict__ out, long long pstride,
             const unsigned char *__restrict__ skip) {
-    __shared__ __attribute__((aligned(16))) double wbuf[2 * core_wstride(R)];
-    lds_char *const wl = lds_ptr(&wbuf[0]);
+    __shared__ __attribute__((aligned(16))) float sink[kWave];
+    lds_char *const wl = lds_ptr(&sink[0]);
     for (;;) {
         const int it = pop_item(counter);
         if (it >= n_items) break;
@@ -668,15 +738,17 @@ __device__ __forceinline__ void fp32_item(const MeshConvDesc &d, char *ws, int p
 
 template <int R>
 __device__ __forceinline__ void multi_core(const MeshConvDesc &d, char *ws, const int4 item, lds_char *wl) {
-    core_item<R>(d.N, d.nD, (const double2 *)(ws + d.cf_bytes), d.core_steps, d.core_ext, d.core_w,
-                 (double2 *)(ws + d.cq_bytes), d.cq_pstride, item, wl);
+    const double2 *const cf = (const double2 *)(ws + d.cf_bytes);
+    double2 *const out = (double2 *)(ws + d.cq_bytes);
+    if (item.x == d.tail_g && d.tail_lw <= 3)
+        narrow_core_item<R>(d.N, d.nD, cf, d.core_steps, d.core_w, out, d.cq_pstride, item, d.tail_lw);
+    else
+        core_item<R>(d.N, d.nD, cf, d.core_steps, d.core_ext, d.core_w, out, d.cq_pstride, item, wl);
 }
 
-// LDS of the one-launch kernel: the largest FP32 step's weights (N = 24: 2 KiB) or the largest
-// core step's (r = 8: 17^2 doubles padded to 3 KiB), double-buffered, or a narrow item's partials
-// and running sums (N = 32: 8 KiB and, for 32 cells, 8 KiB)
+// LDS of the one-launch kernel: a narrow item's; the FP32 steps' weights (N = 24: 2 KiB, double-
+// buffered) take less
 constexpr int kMultiLdsBytes = kNarrowLdsBytes + 256;
-static_assert(2 * core_wstride(kCoreMaxR) * 8 <= kMultiLdsBytes, "core weights exceed the one-launch LDS buffer");
 
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 k_conv_cells_f32_multi(const int4 *__restrict__ items, int n_items, unsigned *__restrict__ counter,
