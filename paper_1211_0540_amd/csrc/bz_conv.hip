@@ -359,7 +359,7 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
 #pragma unroll
             for (int c = 0; c < WL; ++c)
                 __builtin_amdgcn_global_load_lds((const void *)((const char *)(w + PS) + lane * 64 + c * 4096),
-                                                 (void __attribute__((address_space(3))) *)wl, 4, 0, 0);
+                                                 (void __attribute__((address_space(3))) *)rl, 4, 0, 0);
             cells_step_scalar<float, N, SPLIT, CW>(mv, jv, w, wc, pr, pi);
         } else if (WP == 1) {
             // next step's weights pulled into L2 (the LDS copy is discarded); this
@@ -410,6 +410,141 @@ k_conv_cells_f32(const float2 *__restrict__ fh, const int4 *__restrict__ items, 
         const int4 item = items[it];
         const ConvPass cp = pick_pass(ps, (item.y >> 20) & 0xf);
         cells_f32_item<N, FOLD, COMP, WP, RP, SPLIT>(fh, qh, skip, cp, item, wl, rl);
+    }
+}
+
+// One item of a narrow group (NarrowTail: W = 2^lw cells).  The 64 lanes take W cells times
+// S = 64 / W consecutive steps of the row: lane l computes the per-output partials of step
+// s + l / W for cell l % W, with that step's weights, so the row's steps take 1/S as many
+// passes as with one cell on every lane and the other lanes idle (one
+// N=32 cell: 0.30 against 1.41 ms).  The partials go to LDS, half a row at a time, and are then added
+// to the running sums in step order, so the sums are bitwise those of a 64-cell group: a cell's
+// result does not depend on the width of its group.  The weights are read from memory once per
+// 16 bytes and lane (a step's weights are contiguous), kRing reads ahead of their use; that is
+// what bounds the pass: 16 cycles of the CU's L1 per 24 operations, as the broadcasts of LDS.
+// LDS: [N values][64 lanes] partials, [2N values][W cells] running sums (W <= 32).  FP64 items (one partial per output and step, no fold) take the same
+// form at half the read-ahead (one N = 32 cell: 1.1 against
+// 2.9 ms an evaluation).
+template <typename T>
+constexpr int narrow_lds_bytes(int N) {
+    return (int)sizeof(T) * N * (kWave + 2 * (kWave / 2));
+}
+template <typename T>
+struct vec4;
+template <>
+struct vec4<float> {
+    using t = float4;
+};
+template <>
+struct vec4<double> {
+    using t = double4;
+};
+template <typename T, int N>
+__device__ __forceinline__ void narrow_item(const typename cplx<T>::t *fh, double2 *qh, const ConvPass &cp, const int4 item,
+                                            int lw, lds_char *lds, lds_char *sink) {
+    using C = typename cplx<T>::t;
+    using T4 = typename vec4<T>::t;
+    typedef __attribute__((address_space(3))) T lds_t;
+    constexpr bool f32 = sizeof(T) == 4;
+    constexpr int h = N / 2, M = N * N * N, PS = 3 * N * N / 4, FOLD = 16, kRing = f32 ? 14 : 7, SPLIT = f32 ? 2 : 1;
+    constexpr int CB = (int)sizeof(C), CS = f32 ? 3 : 4;   // bytes of a complex value, and their log2
+    const int W = 1 << lw, S = kWave >> lw;
+    const int lane = threadIdx.x, cell = lane & (W - 1), slice = lane >> lw;
+    const int g = item.x, r = item.y & 0xffff, part = (item.y >> 16) & 0xf, s0 = item.z, s1 = item.w;
+    const int k1 = r / N, k2 = r - k1 * N, lo2 = axis_lo(N, k2);
+    double *const out = (double *)(qh + cp.out_off + part * cp.pstride + g * cp.gstride) +
+                        ((size_t)(r - cp.row0) * N << (lw + 1));
+    lds_t *const part_l = (lds_t *)lds, *const run_l = part_l + N * kWave;
+    for (int i = lane; i < 2 * N * W; i += kWave) run_l[i] = 0;
+    if (s0 >= s1) {
+        for (int i = lane; i < 2 * N * W; i += kWave) out[i] = 0.0;
+        return;
+    }
+    const char *const wu = (const char *)uniform_ptr((const T *)cp.w + cp.row_woff[r] + (long long)s0 * PS);
+    const char *const G = (const char *)uniform_ptr(fh + cp.fh_off + (size_t)g * M * kWave);
+    int m1, m2, at = slice < s1 - s0 ? s0 + slice : s1 - 1;   // this lane's step
+    seek_step<N>(k1, k2, at, m1, m2);
+    // weights of the pass at step s pulled into L2, one 128-byte line per lane and load (the copies
+    // in LDS are discarded): a pass reads its S steps' weights far faster than memory answers
+    // one line after the other
+    auto touch = [&](int s) {
+        const int bytes = (s1 - s < S ? s1 - s : S) * (PS * (int)sizeof(T));
+        for (int o = lane * 128; o < bytes; o += kWave * 128)
+            __builtin_amdgcn_global_load_lds((const void *)(wu + (size_t)(s - s0) * (PS * sizeof(T)) + o),
+                                             (void __attribute__((address_space(3))) *)sink, 4, 0, 0);
+    };
+    touch(s0);
+    bool first = true;
+    for (int s = s0; s < s1; s += S) {
+        const int left = s1 - s < S ? s1 - s : S;             // steps of this pass
+        const bool fold = (f32 && (s + S - s0) % FOLD == 0) || s + S >= s1;
+        const unsigned um = (unsigned)((((m1 * N + m2) * N) << lw) + cell) * (unsigned)CB;
+        const unsigned uj = (unsigned)(((((k1 + h - m1) * N + (k2 + h - m2)) * N) << lw) + cell) * (unsigned)CB;
+        const unsigned uw = (unsigned)(at - s0) * (unsigned)(PS * sizeof(T));
+        C mv[N], jv[N];
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            mv[t] = *(const C *)(G + (t << (lw + CS)) + um);
+            jv[t] = *(const C *)(G + (t << (lw + CS)) + uj);
+        }
+        if (s + S < s1) touch(s + S);
+        T4 ring[kRing];
+#pragma unroll
+        for (int i = 0; i < kRing; ++i) ring[i] = *(const T4 *)(wu + uw + i * (4 * sizeof(T)));
+        // the running sums of outputs k3 = K h .. K h + h - 1 from the partials in LDS
+        auto flush = [&](int half) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int i = lane; i < N * W; i += kWave) {
+                const int v = i >> lw, c = i & (W - 1), sw = (v << lw) & (kWave - 1), o = half * N * W + i;
+                T run = run_l[o];
+                for (int q = 0; q < left; ++q) run += part_l[v * kWave + (((q << lw) + c) ^ sw)];
+                if (fold) {
+                    // value v is component v % 2 of output k3 = half h + v / 2
+                    double *const p = out + (((size_t)(half * h + (v >> 1)) << lw) + c) * 2 + (v & 1);
+                    *p = (first ? 0.0 : *p) + (double)run;
+                    run = 0;
+                }
+                run_l[o] = run;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        static_for(std::make_integer_sequence<int, N>{}, [&](auto K) {
+            constexpr int k3 = K;
+            constexpr int mlo = k3 - h + 1 > 0 ? k3 - h + 1 : 0;
+            constexpr int mhi = k3 + h < N - 1 ? k3 + h : N - 1;
+            T sr[SPLIT], si[SPLIT];
+#pragma unroll
+            for (int a = 0; a < SPLIT; ++a) sr[a] = si[a] = 0;
+            static_for(std::make_integer_sequence<int, mhi - mlo + 1>{}, [&](auto I) {
+                constexpr int m3 = mlo + I, j3 = k3 - m3 + h, a = I % SPLIT, t = step_koff(N, k3) + I, c = t / 4;
+                const T4 q = ring[c % kRing];
+                const T wt = t % 4 == 0 ? q.x : t % 4 == 1 ? q.y : t % 4 == 2 ? q.z : q.w;
+                const T px = fma(mv[m3].x, jv[j3].x, -(mv[m3].y * jv[j3].y));
+                const T py = fma(mv[m3].x, jv[j3].y, mv[m3].y * jv[j3].x);
+                sr[a] = fma(wt, px, sr[a]);
+                si[a] = fma(wt, py, si[a]);
+                if constexpr (t % 4 == 3 && c + kRing < PS / 4)
+                    ring[c % kRing] = *(const T4 *)(wu + uw + (c + kRing) * (4 * sizeof(T)));
+            });
+            // lane positions rotated by value, so that lanes reading different values hit different banks
+            constexpr int v = 2 * (k3 % h);
+            part_l[v * kWave + (lane ^ ((v << lw) & (kWave - 1)))] = f32 ? sr[0] + sr[SPLIT - 1] : sr[0];
+            part_l[(v + 1) * kWave + (lane ^ (((v + 1) << lw) & (kWave - 1)))] = f32 ? si[0] + si[SPLIT - 1] : si[0];
+            if constexpr (k3 % h == h - 1) flush(k3 / h);
+        });
+        if (fold) first = false;
+        // this lane's next step
+        const int nx = at + S < s1 ? at + S : s1 - 1;
+        for (m2 += nx - at, at = nx;;) {
+            const int last = cells_m2_last(N, k1, k2, m1);
+            if (m2 <= last) break;
+            m2 -= last - lo2 + 1;
+            ++m1;
+        }
     }
 }
 
@@ -610,130 +745,25 @@ constexpr int multi_weight_path() {
     return N >= 28 ? 3 : 0;
 }
 template <int N>
-__device__ __forceinline__ void multi_item(const MeshConvDesc &d, char *ws, int pass, const int4 item, lds_char *wl) {
+__device__ __forceinline__ void multi_item(const MeshConvDesc &d, char *ws, int pass, const int4 item, lds_char *wl,
+                                           lds_char *sink) {
     const ConvPass cp = d.ps.p[pass];
     cells_f32_item<N, 16, 2, multi_weight_path<N>(), 0, 2>((const float2 *)(ws + d.fh_bytes), (double2 *)(ws + d.qh_bytes), nullptr, cp,
-                                      item, wl, nullptr);
+                                      item, wl, sink);
 }
 
-// One FP32 item of a narrow group (NarrowTail: W = 2^lw cells).  The 64 lanes take W cells times
-// S = 64 / W consecutive steps of the row: lane l computes the per-output partials of step
-// s + l / W for cell l % W, with that step's weights, so the row's steps take 1/S as many
-// passes as with one cell on every lane and the other lanes idle (one
-// N=32 cell: 0.30 against 1.41 ms).  The partials go to LDS, half a row at a time, and are then added
-// to the running sums in step order, so the sums are bitwise those of a 64-cell group: a cell's
-// result does not depend on the width of its group.  The weights are read from memory once per
-// 16 bytes and lane (a step's weights are contiguous), kRing reads ahead of their use; that is
-// what bounds the pass: 16 cycles of the CU's L1 per 24 operations, as the broadcasts of LDS.
-// LDS: [N values][64 lanes] partials, [2N values][W cells] running sums (W <= 32), and 256 bytes
-// that the prefetches write.
-constexpr int kNarrowLdsBytes = 4 * kMaxN * (kWave + 2 * (kWave / 2));
-template <int N>
-__device__ __forceinline__ void narrow_item(const MeshConvDesc &d, char *ws, int pass, const int4 item, lds_char *lds) {
-    constexpr int h = N / 2, M = N * N * N, PS = 3 * N * N / 4, FOLD = 16, kRing = 14;
-    const ConvPass cp = d.ps.p[pass];
-    const int lw = d.tail_lw, W = 1 << lw, S = kWave >> lw;
-    const int lane = threadIdx.x, cell = lane & (W - 1), slice = lane >> lw;
-    const int g = item.x, r = item.y & 0xffff, part = (item.y >> 16) & 0xf, s0 = item.z, s1 = item.w;
-    const int k1 = r / N, k2 = r - k1 * N, lo2 = axis_lo(N, k2);
-    double *const out = (double *)((double2 *)(ws + d.qh_bytes) + cp.out_off + part * cp.pstride + g * cp.gstride) +
-                        ((size_t)(r - cp.row0) * N << (lw + 1));
-    lds_float *const part_l = (lds_float *)lds, *const run_l = part_l + N * kWave;
-    for (int i = lane; i < 2 * N * W; i += kWave) run_l[i] = 0.f;
-    if (s0 >= s1) {
-        for (int i = lane; i < 2 * N * W; i += kWave) out[i] = 0.0;
-        return;
-    }
-    const char *const wu = (const char *)uniform_ptr((const float *)cp.w + cp.row_woff[r] + (long long)s0 * PS);
-    const char *const G = (const char *)uniform_ptr((const float2 *)(ws + d.fh_bytes) + cp.fh_off + (size_t)g * M * kWave);
-    int m1, m2, at = slice < s1 - s0 ? s0 + slice : s1 - 1;   // this lane's step
-    seek_step<N>(k1, k2, at, m1, m2);
-    // weights of the pass at step s pulled into L2, one 128-byte line per lane and load (the copies
-    // in LDS are discarded): a pass reads its S steps' weights far faster than memory answers
-    // one line after the other
-    auto touch = [&](int s) {
-        const int bytes = (s1 - s < S ? s1 - s : S) * (PS * 4);
-        for (int o = lane * 128; o < bytes; o += kWave * 128)
-            __builtin_amdgcn_global_load_lds((const void *)(wu + (size_t)(s - s0) * (PS * 4) + o),
-                                             (void __attribute__((address_space(3))) *)(lds + kNarrowLdsBytes), 4, 0, 0);
-    };
-    touch(s0);
-    bool first = true;
-    for (int s = s0; s < s1; s += S) {
-        const int left = s1 - s < S ? s1 - s : S;             // steps of this pass
-        const bool fold = ((s + S - s0) % FOLD) == 0 || s + S >= s1;
-        const unsigned um = (unsigned)((((m1 * N + m2) * N) << lw) + cell) * 8u;
-        const unsigned uj = (unsigned)(((((k1 + h - m1) * N + (k2 + h - m2)) * N) << lw) + cell) * 8u;
-        const unsigned uw = (unsigned)(at - s0) * (PS * 4u);
-        float2 mv[N], jv[N];
-#pragma unroll
-        for (int t = 0; t < N; ++t) {
-            mv[t] = *(const float2 *)(G + (t << (lw + 3)) + um);
-            jv[t] = *(const float2 *)(G + (t << (lw + 3)) + uj);
-        }
-        if (s + S < s1) touch(s + S);
-        float4 ring[kRing];
-#pragma unroll
-        for (int i = 0; i < kRing; ++i) ring[i] = *(const float4 *)(wu + uw + i * 16);
-        // the running sums of outputs k3 = K h .. K h + h - 1 from the partials in LDS
-        auto flush = [&](int half) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            for (int i = lane; i < N * W; i += kWave) {
-                const int v = i >> lw, c = i & (W - 1), sw = (v << lw) & (kWave - 1), o = half * N * W + i;
-                float run = run_l[o];
-                for (int q = 0; q < left; ++q) run += part_l[v * kWave + (((q << lw) + c) ^ sw)];
-                if (fold) {
-                    // value v is component v % 2 of output k3 = half h + v / 2
-                    double *const p = out + (((size_t)(half * h + (v >> 1)) << lw) + c) * 2 + (v & 1);
-                    *p = (first ? 0.0 : *p) + (double)run;
-                    run = 0.f;
-                }
-                run_l[o] = run;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        };
-        static_for(std::make_integer_sequence<int, N>{}, [&](auto K) {
-            constexpr int k3 = K;
-            constexpr int mlo = k3 - h + 1 > 0 ? k3 - h + 1 : 0;
-            constexpr int mhi = k3 + h < N - 1 ? k3 + h : N - 1;
-            float sr[2] = {0.f, 0.f}, si[2] = {0.f, 0.f};
-            static_for(std::make_integer_sequence<int, mhi - mlo + 1>{}, [&](auto I) {
-                constexpr int m3 = mlo + I, j3 = k3 - m3 + h, a = I % 2, t = step_koff(N, k3) + I, c = t / 4;
-                const float4 q = ring[c % kRing];
-                const float wt = t % 4 == 0 ? q.x : t % 4 == 1 ? q.y : t % 4 == 2 ? q.z : q.w;
-                const float px = fma(mv[m3].x, jv[j3].x, -(mv[m3].y * jv[j3].y));
-                const float py = fma(mv[m3].x, jv[j3].y, mv[m3].y * jv[j3].x);
-                sr[a] = fma(wt, px, sr[a]);
-                si[a] = fma(wt, py, si[a]);
-                if constexpr (t % 4 == 3 && c + kRing < PS / 4)
-                    ring[c % kRing] = *(const float4 *)(wu + uw + (c + kRing) * 16);
-            });
-            // lane positions rotated by value, so that lanes reading different values hit different banks
-            constexpr int v = 2 * (k3 % h);
-            part_l[v * kWave + (lane ^ ((v << lw) & (kWave - 1)))] = sr[0] + sr[1];
-            part_l[(v + 1) * kWave + (lane ^ (((v + 1) << lw) & (kWave - 1)))] = si[0] + si[1];
-            if constexpr (k3 % h == h - 1) flush(k3 / h);
-        });
-        if (fold) first = false;
-        // this lane's next step
-        const int nx = at + S < s1 ? at + S : s1 - 1;
-        for (m2 += nx - at, at = nx;;) {
-            const int last = cells_m2_last(N, k1, k2, m1);
-            if (m2 <= last) break;
-            m2 -= last - lo2 + 1;
-            ++m1;
-        }
-    }
-}
+// LDS of the one-launch kernel: a narrow item's (the FP32 steps' weights, N = 24 2 KiB double-buffered,
+// take less), then 256 bytes that the prefetches into L2 write and nothing reads
+constexpr int kMultiSink = narrow_lds_bytes<float>(kMaxN), kMultiLdsBytes = kMultiSink + 256;
 
 template <int N>
 __device__ __forceinline__ void fp32_item(const MeshConvDesc &d, char *ws, int pass, const int4 item, lds_char *lds) {
-    if (item.x == d.tail_g) narrow_item<N>(d, ws, pass, item, lds);
-    else multi_item<N>(d, ws, pass, item, lds);
+    lds_char *const sink = lds + kMultiSink;
+    if (item.x == d.tail_g)
+        narrow_item<float, N>((const float2 *)(ws + d.fh_bytes), (double2 *)(ws + d.qh_bytes), d.ps.p[pass], item, d.tail_lw, lds,
+                              sink);
+    else
+        multi_item<N>(d, ws, pass, item, lds, sink);
 }
 
 template <int R>
@@ -745,10 +775,6 @@ __device__ __forceinline__ void multi_core(const MeshConvDesc &d, char *ws, cons
     else
         core_item<R>(d.N, d.nD, cf, d.core_steps, d.core_ext, d.core_w, out, d.cq_pstride, item, wl);
 }
-
-// LDS of the one-launch kernel: a narrow item's; the FP32 steps' weights (N = 24: 2 KiB, double-
-// buffered) take less
-constexpr int kMultiLdsBytes = kNarrowLdsBytes + 256;
 
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 k_conv_cells_f32_multi(const int4 *__restrict__ items, int n_items, unsigned *__restrict__ counter,
@@ -767,14 +793,14 @@ k_conv_cells_f32_multi(const int4 *__restrict__ items, int n_items, unsigned *__
         if (item.y & kCoreItemBit) {
             const int4 ci = make_int4(item.x, item.y & 0xffffff, item.z, item.w);
             switch (d.core_r) {
-            case 1: multi_core<1>(d, ws, ci, wl); break;
-            case 2: multi_core<2>(d, ws, ci, wl); break;
-            case 3: multi_core<3>(d, ws, ci, wl); break;
-            case 4: multi_core<4>(d, ws, ci, wl); break;
-            case 5: multi_core<5>(d, ws, ci, wl); break;
-            case 6: multi_core<6>(d, ws, ci, wl); break;
-            case 7: multi_core<7>(d, ws, ci, wl); break;
-            default: multi_core<8>(d, ws, ci, wl); break;
+            case 1: multi_core<1>(d, ws, ci, wl + kMultiSink); break;
+            case 2: multi_core<2>(d, ws, ci, wl + kMultiSink); break;
+            case 3: multi_core<3>(d, ws, ci, wl + kMultiSink); break;
+            case 4: multi_core<4>(d, ws, ci, wl + kMultiSink); break;
+            case 5: multi_core<5>(d, ws, ci, wl + kMultiSink); break;
+            case 6: multi_core<6>(d, ws, ci, wl + kMultiSink); break;
+            case 7: multi_core<7>(d, ws, ci, wl + kMultiSink); break;
+            default: multi_core<8>(d, ws, ci, wl + kMultiSink); break;
             }
             continue;
         }
@@ -793,15 +819,22 @@ k_conv_cells_f32_multi(const int4 *__restrict__ items, int n_items, unsigned *__
 // ---------------------------------------------------------------------------
 // Batched FP64.
 // ---------------------------------------------------------------------------
+// The weights arrive by scalar loads from N = 24 on (190 N = 32 cells 10.0 -> 8.0 ms a launch, 200 N = 24
+// cells 2.76 -> 2.41 ms an evaluation): with one wavefront per SIMD the broadcast LDS reads take 32 cycles per
+// pair and CU, the FP64 operations of the four SIMDs 24.  Below, two or more wavefronts share a SIMD and the
+// wait for a chunk of 16 weights costs more (N = 20 1.06 against 1.12 ms, N = 16 330 against 352 us).
 template <int N>
 __global__ void __launch_bounds__(64) k_conv_cells_f64(const double2 *__restrict__ fh, const int4 *__restrict__ items,
                                                        int n_items, unsigned *__restrict__ counter,
                                                        double2 *__restrict__ qh,
-                                                       const unsigned char *__restrict__ skip, const ConvPasses ps) {
+                                                       const unsigned char *__restrict__ skip, const ConvPasses ps,
+                                                       const NarrowTail nt) {
     constexpr int h = N / 2, M = N * N * N, PS = 3 * N * N / 4;
-    constexpr int CH = (PS * 8 + 1023) / 1024;
-    __shared__ __attribute__((aligned(16))) double wbuf[2][CH * 128];
-    lds_char *const wl = lds_ptr(&wbuf[0][0]);
+    constexpr bool kScalar = N >= 24;
+    constexpr int CH = (PS * 8 + 1023) / 1024, CW = weight_chunk<double, N>(), WL = (PS * 8 + 4095) / 4096;
+    constexpr int kLds = 2 * CH * 1024 > narrow_lds_bytes<double>(N) ? 2 * CH * 1024 : narrow_lds_bytes<double>(N);
+    __shared__ __attribute__((aligned(16))) double wbuf[(kLds + 256) / 8];
+    lds_char *const wl = lds_ptr(&wbuf[0]), *const sink = wl + kLds;   // sink: written by the prefetches into L2
     const int lane = threadIdx.x;
     for (;;) {
         const int it = pop_item(counter);
@@ -817,6 +850,10 @@ __global__ void __launch_bounds__(64) k_conv_cells_f64(const double2 *__restrict
             for (int t = 0; t < N; ++t) out[t * kWave] = make_double2(0.0, 0.0);
             continue;
         }
+        if (g == nt.g) {
+            narrow_item<double, N>(fh, qh, cp, item, nt.lw, wl, sink);
+            continue;
+        }
         const double *w = (const double *)cp.w + cp.row_woff[r] + (long long)s0 * PS;
         const double2 *F = fh + cp.fh_off + (size_t)g * M * kWave + lane;
         double pr[N], pi[N];
@@ -825,24 +862,38 @@ __global__ void __launch_bounds__(64) k_conv_cells_f64(const double2 *__restrict
         int m1, m2;
         seek_step<N>(k1, k2, s0, m1, m2);
         const int lo2 = axis_lo(N, k2);
-        prefetch_weights<CH>(w, wl);
-        __builtin_amdgcn_s_waitcnt(0);
+        WeightChunk<double, CW> wc;
+        if constexpr (kScalar) {
+            w = uniform_ptr(w);
+            wc = load_chunk<double, CW>(w);
+        } else {
+            prefetch_weights<CH>(w, wl);
+            __builtin_amdgcn_s_waitcnt(0);
+        }
         int buf = 0;
         for (int s = s0; s < s1; ++s) {
             const int j1 = k1 + h - m1, j2 = k2 + h - m2;
-            prefetch_weights<CH>(w + PS, wl + (buf ^ 1) * CH * 1024);
+            if constexpr (!kScalar) prefetch_weights<CH>(w + PS, wl + (buf ^ 1) * CH * 1024);
             double2 mv[N], jv[N];
             load_row<double, N>(F + (size_t)((m1 * N + m2) * N) * kWave, mv);
             load_row<double, N>(F + (size_t)((j1 * N + j2) * N) * kWave, jv);
-            if (!cp.zero_planes || (m2 != 0 && j2 != 0))
-                cells_step<double, N, 1>(mv, jv, (const double *)wbuf[buf], pr, pi);
+            if constexpr (kScalar) {
+                // the next step's weights pulled into L2 (64 bytes a lane, the LDS copy is discarded)
+#pragma unroll
+                for (int c = 0; c < WL; ++c)
+                    __builtin_amdgcn_global_load_lds((const void *)((const char *)(w + PS) + lane * 64 + c * 4096),
+                                                     (void __attribute__((address_space(3))) *)sink, 4, 0, 0);
+                cells_step_scalar<double, N, 1, CW>(mv, jv, w, wc, pr, pi);
+            } else if (!cp.zero_planes || (m2 != 0 && j2 != 0)) {
+                cells_step<double, N, 1>(mv, jv, (const lds_double *)(wl + buf * CH * 1024), pr, pi);
+            }
             w += PS;
             buf ^= 1;
             if (++m2 > cells_m2_last(N, k1, k2, m1)) {
                 ++m1;
                 m2 = lo2;
             }
-            __builtin_amdgcn_s_waitcnt(0);
+            if constexpr (!kScalar) __builtin_amdgcn_s_waitcnt(0);
         }
 #pragma unroll
         for (int t = 0; t < N; ++t) out[t * kWave] = make_double2(pr[t], pi[t]);
@@ -960,7 +1011,7 @@ hipError_t cells_f32_variant(const CellsLaunch &p, unsigned grid, hipStream_t s)
 template <int N>
 hipError_t cells_f64_launch(const CellsLaunch &p, unsigned grid, hipStream_t s) {
     hipLaunchKernelGGL((k_conv_cells_f64<N>), dim3(grid), dim3(64), 0, s, (const double2 *)p.fh, p.items,
-                       p.n_items, p.counter, p.qh, p.skip, p.passes);
+                       p.n_items, p.counter, p.qh, p.skip, p.passes, p.tail);
     return hipGetLastError();
 }
 

@@ -367,6 +367,7 @@ struct CellsLaunch {
     int variant;                 // tuning variant
     const unsigned char *skip;   // device, per group: 1 = outputs not needed (may be NULL)
     ConvPasses passes;
+    NarrowTail tail;             // FP64: the narrow last group
 };
 // Batched FP32 convolution of several meshes in one persistent launch: item words carry the
 // mesh index (bits 24..27) into a device table of descriptors (uploaded when the weights are

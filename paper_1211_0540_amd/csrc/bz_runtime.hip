@@ -765,8 +765,8 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
             if (grid_of_cell[c] == gi) p.cells.push_back(c);
         if (p.cells.empty()) continue;
         p.groups = (int)((p.cells.size() + kWave - 1) / kWave);
-        // a last group of at most 32 cells: W = 4, 8, 16 or 32 lanes hold its cells in the one launch,
-        // which takes 64 / W steps of a row at once (FP32 items of one group, W = 64 / 32 / 4: N = 32
+        // a last group of at most 32 cells: W = 4, 8, 16 or 32 lanes hold its cells in the one launch
+        // and the FP64 kernel, which take 64 / W steps of a row at once (FP32 items of one group, W = 64 / 32 / 4: N = 32
         // 1.41 / 1.24 / 0.30 ms, N = 24 345 / 286 / 104 us, N = 16 80 / 74 / 44 us; above 32 cells
         // there is no second step to take)
         const int rest = (int)(p.cells.size() % kWave);
@@ -1400,6 +1400,8 @@ static bz_status collide_batched(bz_batch b, const double *d_f, double *d_Qt, ch
     // skip and slot_off come with one-mesh batches (the gated closure); the group index of an
     // item is then the skip index
     const bool merged = b->d_multi_items && !b->per_mesh_now;
+    // the one launch and the FP64 kernel take a narrow last group, the per-mesh FP32 variants do not
+    auto tail_of = [&](const Part &p) { return merged || f64 ? p.tail : NarrowTail{-1, 6}; };
     for (const Part &p : b->parts) {
         const CoreSched &cs = p.g->sched.core;
         const long long *f_off = slot_off ? slot_off : p.d_f_off;
@@ -1407,8 +1409,7 @@ static bz_status collide_batched(bz_batch b, const double *d_f, double *d_Qt, ch
         const CoreFill cfill{p.core ? (double2 *)(ws + p.ws_cf) : nullptr, p.d_disk_idx, cs.nD, cs.r, cs.r2};
         BZ_HIP(launch_dft_forward_grouped(p.g->N, p.g->L, (int)p.cells.size(), d_f, f_off, scratch,
                                           (double2 *)(ws + p.ws_qh), ws + p.ws_fh, !f64, p.herm ? 4 : 1, cfill, skip,
-                                          merged ? p.tail : NarrowTail{-1, 6},
-                                          merged ? (unsigned *)(ws + b->ws_mcounter) : nullptr, s),
+                                          tail_of(p), merged ? (unsigned *)(ws + b->ws_mcounter) : nullptr, s),
                "forward transform");
     }
     // the FP64 cores: in the one-launch queue, or else on their own stream after the forward
@@ -1449,7 +1450,7 @@ static bz_status collide_batched(bz_batch b, const double *d_f, double *d_Qt, ch
     } else {
         for (const Part &p : b->parts) {
             CellsLaunch cl{p.g->N, ws + p.ws_fh, p.d_items, p.n_items, (unsigned *)(ws + p.ws_counter),
-                           (double2 *)(ws + p.ws_qh), p.variant, skip, conv_passes(p, f64)};
+                           (double2 *)(ws + p.ws_qh), p.variant, skip, conv_passes(p, f64), tail_of(p)};
             std::pair<hipEvent_t, hipEvent_t> ev{};
             if (b->timing) {
                 if (!timer_pair(b, ev)) return fail(BZ_EDEVICE, "bz_collide_batch: hipEventCreate failed");
@@ -1470,7 +1471,7 @@ static bz_status collide_batched(bz_batch b, const double *d_f, double *d_Qt, ch
         // groups whose cells are all served by the closure (skip) need no transforms: the
         // closure writes their outputs
         BZ_HIP(launch_dft_inverse_grouped(p.g->N, p.g->L, (int)p.cells.size(), qh, p.parts, pstride, herm, cadd,
-                                          scratch, qh, d_Qt, f_off, skip, merged ? p.tail : NarrowTail{-1, 6}, s),
+                                          scratch, qh, d_Qt, f_off, skip, tail_of(p), s),
                "inverse transform");
     }
     return BZ_OK;

@@ -38,3 +38,19 @@ def test_narrow_groups_are_bitwise_the_wide_ones(dev, N, L, n, schedule):
         c.close()
     assert np.all(np.isfinite(out[0]))
     assert np.array_equal(out[0], out[1])
+
+
+# FP64: a narrow item adds the steps' partials in step order as well (bitwise)
+@pytest.mark.parametrize("N,L,n", [(8, 4.0, 2), (12, 5.0, 67), (16, 6.0, 32), (20, 6.0, 6), (24, 7.0, 17), (28, 7.0, 4),
+                                   (32, 8.0, 9)])
+def test_narrow_groups_fp64_are_bitwise_the_wide_ones(dev, N, L, n):
+    cells = list(W.random_smooth_cells(n, N, L, seed=400 + N, umax=0.5))
+    wide = cells + [cells[0]] * (33 + n // 64 * 64 - n if n % 64 < 33 else 0)   # a last group of 33 cells is wide
+    out = []
+    for fs in (cells, wide):
+        c = bz.Collision([(N, L, 1.0)], [0] * len(fs), "batched_f64", weights_cache=_WCACHE, fine_split=True)
+        f = torch.from_numpy(c.pack(fs)).to(dev)
+        out.append(c.collide(f).cpu().numpy()[:n * N ** 3])
+        c.close()
+    assert np.all(np.isfinite(out[0]))
+    assert np.array_equal(out[0], out[1])
