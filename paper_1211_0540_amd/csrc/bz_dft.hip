@@ -425,16 +425,18 @@ __global__ void __launch_bounds__(256) k_dftg_fwd3(const double2 *__restrict__ T
 // Inverse, axis 1: Qhat(k1, k2, k3) of line (k2, k3) from the buffers of the convolution, then the
 // transform -> S (j1, k2, k3).  The line is assembled kAsm outputs at a time, the loads of one
 // buffer for all of them issued together: a load per output and buffer after the other left the
-// pass waiting for memory (N = 16, one group with 8 partial buffers: 57 us), all N outputs of a
-// line at once do not fit the registers.
+// pass waiting for memory (N = 16, one group with 8 partial buffers: 57 us, 31 with four, 26 with eight
+// at once), all N outputs of a line do not fit the registers, nor eight of a longer line at three
+// wavefronts per SIMD.
 // ---------------------------------------------------------------------------
-constexpr int kAsm = 4;
+template <int N>
+constexpr int kAsmOf = N == 8 || N == 16 ? 8 : 4;
 
 // The FP64 core sum (CoreAdd; core NULL when off) of outputs k1 = K0 .. K0 + kAsm - 1, added to every
 // output within 2cr of the centre.  The core holds it for the direct rows and for k3 = 0 of the derived
 // rows; elsewhere a derived output is the conjugate of its mirror N - k (the core pairs are
 // interior, and the weights even).  gl: the lane's element 0 of the group's core lines.
-template <int N, int K0>
+template <int N, int K0, int kAsm = kAsmOf<N>>
 __device__ __forceinline__ void add_core(double2 (&x)[N], const CoreAdd &ca, size_t gl, int k2, int k3) {
     constexpr int h = N / 2;
     const int cr = ca.r;
@@ -474,7 +476,7 @@ __device__ __forceinline__ void add_core(double2 (&x)[N], const CoreAdd &ca, siz
 //   derived row, k3 >= 1:       Qhat = conj I(k') + E(k),   k' = N - k
 // E(k) is the edge sum: E1 at (k1, k2, k3) if k1 < N/2, E2 at (k2, k1, k3) if k2 < N/2,
 // E3 at (k3, k1, k2) if k3 < N/2.
-template <int N, int K0, typename L>
+template <int N, int K0, typename L, int kAsm = kAsmOf<N>>
 __device__ __forceinline__ void assemble_herm(double2 (&x)[N], const double2 *__restrict__ qh, int nA,
                                               long long pstride, const L &l, int k2, int k3) {
     constexpr int h = N / 2, M = N * N * N;
@@ -535,7 +537,7 @@ __device__ __forceinline__ void assemble_herm(double2 (&x)[N], const double2 *__
 }
 
 // outputs K0 .. K0 + kAsm - 1 of the full-sum schedule: the sum of the partial buffers
-template <int N, int K0, typename L>
+template <int N, int K0, typename L, int kAsm = kAsmOf<N>>
 __device__ __forceinline__ void assemble_full(double2 (&x)[N], const double2 *__restrict__ qh, int nparts,
                                               long long pstride, const L &l) {
     const size_t off = (size_t)l.g * N * N * N * kWave + l.at(l.line) + l.cell;
@@ -556,7 +558,8 @@ template <int N, bool HERM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 k_dftg_inv1(const double2 *__restrict__ qh, int nparts, long long pstride, const CoreAdd core,
             double2 *__restrict__ S, const unsigned char *__restrict__ skip, const NarrowTail nt) {
-    constexpr int M = N * N * N, h = N / 2;
+    constexpr int M = N * N * N, h = N / 2, kAsm = kAsmOf<N>;
+    static_assert(N % kAsm == 0, "the line is assembled in whole chunks");
     grouped_lane<N>(nt, skip, [&](const auto &l) {
         const int k2 = l.line / N, k3 = l.line - k2 * N;
         const bool cores = core.core && abs(k2 - h) <= 2 * core.r && abs(k3 - h) <= 2 * core.r;
