@@ -250,61 +250,102 @@ __global__ void k_fill_u32(unsigned *p, int n, unsigned v) {
 }
 
 // ---------------------------------------------------------------------------
-// Diagnostics (Sec. 5: bulk velocity, marginal near the wall).  One block of
-// 256 threads per cell, fixed reduction order: density and bulk velocity in a
-// first pass, the temperature about that velocity in a second.
+// Diagnostics (Sec. 5: bulk velocity, marginal near the wall).  One block per
+// cell, fixed reduction order: density and bulk velocity in a first pass, the
+// temperature about that velocity in a second.  A cell is one block's work, so
+// what a thread waits for in turn sets the time: 1024 threads hold the cell in
+// registers over both passes (every load issued at once, N a template parameter),
+// and the second level of a sum is one LDS read and four shuffles (72 N = 24
+// cells and the wall marginal 25 -> 15 us against 256 threads that read the cell twice).
 // ---------------------------------------------------------------------------
-__device__ inline double block_sum256(double x, double *red) {
-    x = wave_sum(x);
+constexpr int kMomThreads = 1024;
+template <int n>
+__device__ inline void block_sums(double (&x)[n], double (*red)[kMomThreads / 64]) {
+    constexpr int W = kMomThreads / 64;
+#pragma unroll
+    for (int i = 0; i < n; ++i) x[i] = wave_sum(x[i]);
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int i = 0; i < n; ++i) red[i][threadIdx.x >> 6] = x[i];
+    }
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    return red[0] + red[1] + red[2] + red[3];
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        x[i] = red[i][threadIdx.x % W];
+#pragma unroll
+        for (int o = W / 2; o > 0; o >>= 1) x[i] += __shfl_xor(x[i], o);
+    }
 }
 
-__global__ void __launch_bounds__(256) k_cell_moments(const double *__restrict__ f, const long long *__restrict__ off,
-                                                      const int *__restrict__ nn, const double *__restrict__ dvs,
-                                                      double *__restrict__ mom) {
-    __shared__ double red[4];
-    const int c = blockIdx.x, N = nn[c], M = N * N * N, h = N / 2;
-    const double dv = dvs[c];
-    const double *F = f + off[c];
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    for (int k = threadIdx.x; k < M; k += 256) {
-        const double x = F[k];
-        a0 += x;
-        a1 = fma(dv * (k / (N * N) - h), x, a1);
-        a2 = fma(dv * ((k / N) % N - h), x, a2);
-        a3 = fma(dv * (k % N - h), x, a3);
+template <int N>
+__device__ __forceinline__ void moments_of(const double *__restrict__ F, double dv, double *__restrict__ o,
+                                           double (*red)[kMomThreads / 64]) {
+    constexpr int M = N * N * N, PER = (M + kMomThreads - 1) / kMomThreads, h = N / 2;
+    double x[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int k = threadIdx.x + i * kMomThreads;
+        x[i] = k < M ? F[k] : 0.0;
     }
-    const double rho = block_sum256(a0, red);
-    const double u1 = block_sum256(a1, red) / rho, u2 = block_sum256(a2, red) / rho, u3 = block_sum256(a3, red) / rho;
-    double e = 0.0;
-    for (int k = threadIdx.x; k < M; k += 256) {
+    // (each pass recomputes its indices from an opaque copy of the thread index: kept live they spill)
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    int t0 = threadIdx.x;
+    asm volatile("" : "+v"(t0));
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int k = t0 + i * kMomThreads;
+        if (k >= M) continue;
+        a[0] += x[i];
+        a[1] = fma(dv * (k / (N * N) - h), x[i], a[1]);
+        a[2] = fma(dv * ((k / N) % N - h), x[i], a[2]);
+        a[3] = fma(dv * (k % N - h), x[i], a[3]);
+    }
+    block_sums(a, red);
+    const double rho = a[0], u1 = a[1] / rho, u2 = a[2] / rho, u3 = a[3] / rho;
+    double e[1] = {0.0};
+    int t1 = threadIdx.x;
+    asm volatile("" : "+v"(t1));
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int k = t1 + i * kMomThreads;
+        if (k >= M) continue;
         const double w1 = dv * (k / (N * N) - h) - u1, w2 = dv * ((k / N) % N - h) - u2, w3 = dv * (k % N - h) - u3;
-        e = fma(w1 * w1 + w2 * w2 + w3 * w3, F[k], e);
+        e[0] = fma(w1 * w1 + w2 * w2 + w3 * w3, x[i], e[0]);
     }
-    const double E = block_sum256(e, red);
+    block_sums(e, red + 4);
     if (threadIdx.x == 0) {
-        double *o = mom + 5 * (size_t)c;
         o[0] = rho * dv * dv * dv;
         o[1] = u1;
         o[2] = u2;
         o[3] = u3;
-        o[4] = E / (3.0 * rho);
+        o[4] = e[0] / (3.0 * rho);
     }
 }
 
-// marginal of one cell in v1: out[k1] = dv^2 sum_{k2,k3} f(k1, k2, k3); one wavefront per k1
-__global__ void __launch_bounds__(256) k_marginal_v1(int N, double dv, const double *__restrict__ F,
-                                                     double *__restrict__ out) {
-    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int k1 = wid; k1 < N; k1 += 4) {
-        double s = 0.0;
-        for (int t = lane; t < N * N; t += 64) s += F[(size_t)k1 * N * N + t];
-        s = wave_sum(s);
-        if (lane == 0) out[k1] = s * dv * dv;
+__global__ void __launch_bounds__(kMomThreads) k_cell_moments(const double *__restrict__ f, const long long *__restrict__ off,
+                                                              const int *__restrict__ nn, const double *__restrict__ dvs,
+                                                              double *__restrict__ mom) {
+    __shared__ double red[5][kMomThreads / 64];
+    const int c = blockIdx.x;
+    const double *F = f + off[c];
+    double *o = mom + 5 * (size_t)c;
+    switch (nn[c]) {
+#define BZ_MOM(n) \
+    case n: moments_of<n>(F, dvs[c], o, red); break;
+        BZ_MOM(8) BZ_MOM(12) BZ_MOM(16) BZ_MOM(20) BZ_MOM(24) BZ_MOM(28) BZ_MOM(32)
+#undef BZ_MOM
     }
+}
+
+// marginal of one cell in v1: out[k1] = dv^2 sum_{k2,k3} f(k1, k2, k3); one wavefront per block and k1
+__global__ void __launch_bounds__(64) k_marginal_v1(int N, double dv, const double *__restrict__ F,
+                                                    double *__restrict__ out) {
+    const int k1 = blockIdx.x;
+    double s = 0.0;
+#pragma unroll 8
+    for (int t = threadIdx.x; t < N * N; t += 64) s += F[(size_t)k1 * N * N + t];
+    s = wave_sum(s);
+    if (threadIdx.x == 0) out[k1] = s * dv * dv;
 }
 
 // ---------------------------------------------------------------------------
@@ -490,12 +531,12 @@ hipError_t launch_build_e3(int N, const long long *d_row_woff, const long long *
 hipError_t launch_cell_moments(int ncells, const double *f, const long long *off, const int *nn, const double *dvs,
                                double *mom, hipStream_t s) {
     if (ncells <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cell_moments, dim3(ncells), dim3(256), 0, s, f, off, nn, dvs, mom);
+    hipLaunchKernelGGL(k_cell_moments, dim3(ncells), dim3(kMomThreads), 0, s, f, off, nn, dvs, mom);
     return hipGetLastError();
 }
 
 hipError_t launch_marginal_v1(int N, double dv, const double *f, double *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_marginal_v1, dim3(1), dim3(256), 0, s, N, dv, f, out);
+    hipLaunchKernelGGL(k_marginal_v1, dim3(N), dim3(64), 0, s, N, dv, f, out);
     return hipGetLastError();
 }
 
