@@ -776,15 +776,23 @@ __device__ __forceinline__ void multi_core(const MeshConvDesc &d, char *ws, cons
         core_item<R>(d.N, d.nD, cf, d.core_steps, d.core_ext, d.core_w, out, d.cq_pstride, item, wl);
 }
 
+// The work queues of the one launch (MultiQueues): a wavefront takes items from its XCD's queue, then
+// from the others in turn.
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
-k_conv_cells_f32_multi(const int4 *__restrict__ items, int n_items, unsigned *__restrict__ counter,
+k_conv_cells_f32_multi(const int4 *__restrict__ items, const MultiQueues mq, unsigned *__restrict__ counter,
                        const MeshConvDesc *__restrict__ desc, char *__restrict__ ws,
                        const unsigned char *__restrict__ skip) {
     __shared__ __attribute__((aligned(16))) double wbuf[kMultiLdsBytes / 8];
     lds_char *const wl = lds_ptr(&wbuf[0]);
+    constexpr int kXccId = 20 | (3 << 11);   // hardware register 20, XCC_ID, bits 0..3
+    int q = mq.n > 1 ? (int)(__builtin_amdgcn_s_getreg(kXccId) % kMultiQueues) : 0, tried = 0;
     for (;;) {
-        const int it = pop_item(counter);
-        if (it >= n_items) break;
+        const int it = mq.start[q] + pop_item(counter + q * kQueueStride);
+        if (it >= mq.start[q + 1]) {
+            if (++tried >= mq.n) break;
+            q = q + 1 < mq.n ? q + 1 : 0;
+            continue;
+        }
         const int4 item = items[it];
         // a group whose cells are all served elsewhere: nothing reads its outputs
         if (skip && skip[item.x]) continue;
@@ -1074,7 +1082,7 @@ hipError_t core_launch(const CoreLaunch &p, unsigned grid, hipStream_t s) {
 
 hipError_t launch_conv_cells_multi(const MultiLaunch &p, hipStream_t s) {
     if (p.n_items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_conv_cells_f32_multi, dim3(persistent_grid(p.n_items)), dim3(64), 0, s, p.items, p.n_items,
+    hipLaunchKernelGGL(k_conv_cells_f32_multi, dim3(persistent_grid(p.n_items)), dim3(64), 0, s, p.items, p.queues,
                        p.counter, p.desc, p.ws, p.skip);
     return hipGetLastError();
 }

@@ -371,7 +371,7 @@ __global__ void __launch_bounds__(256) k_dftg_mid(const double2 *__restrict__ S,
 // with copies = 4 also fhat with the axes ordered (2, 1, 3) and (3, 1, 2), and fhat with every k_d = 0
 // plane set to zero (axes in order), copy_stride elements apart
 // With cf non-NULL it also writes the FP64 rows of the low-frequency core (CoreFill), whose lines
-// hold 64 cells in every group.  It clears the work-queue counter of the convolution that follows.
+// hold 64 cells in every group.  It clears the work-queue counters of the convolution that follows.
 template <int N, typename Out>
 __global__ void __launch_bounds__(256) k_dftg_fwd3(const double2 *__restrict__ T, int nc, double scale,
                                                    Out *__restrict__ fh, int copies, long long copy_stride,
@@ -379,7 +379,7 @@ __global__ void __launch_bounds__(256) k_dftg_fwd3(const double2 *__restrict__ T
                                                    int nD, int cr, int cr2, const unsigned char *__restrict__ skip,
                                                    const NarrowTail nt, unsigned *__restrict__ counter) {
     constexpr int M = N * N * N;
-    if (counter && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *counter = 0;
+    if (counter && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kMultiQueues * kQueueStride) counter[threadIdx.x] = 0;
     grouped_lane<N>(nt, skip, [&](const auto &l) {
         const int k2 = l.line / N, k3 = l.line - k2 * N;
         const size_t gl = (size_t)l.g * M * kWave + l.cell, off = gl + l.at(l.line);

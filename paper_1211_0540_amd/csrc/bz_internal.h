@@ -391,10 +391,21 @@ struct MeshConvDesc {
 constexpr int kCoreItemBit = 1 << 28;
 // most step pieces of one core row (bits 20..23 of a core item's row word)
 constexpr int kCoreMaxParts = 4;
+// The item list in n queues, one per accelerator complex die (XCD) or one in all: queue q holds the items
+// [start[q], start[q + 1]) and takes them by counter[q kQueueStride].  The cells of a group share
+// their fhat rows, so a group's items go to as few XCDs as its share of the work fills: an XCD's
+// L2 (4 MB) then meets one or two groups' rows instead of all (one copy of a group: N = 16 2.1 MB,
+// N = 24 7 MB, N = 32 16.8 MB).
+constexpr int kMultiQueues = 8, kQueueStride = 8;
+struct MultiQueues {
+    int n;
+    int start[kMultiQueues + 1];
+};
 struct MultiLaunch {
     const int4 *items;
     int n_items;
-    unsigned *counter;           // device, zero (cleared by the forward transforms)
+    MultiQueues queues;
+    unsigned *counter;           // device, kMultiQueues kQueueStride words, zero (cleared by the forward transforms)
     const MeshConvDesc *desc;    // device
     char *ws;                    // the call's workspace
     const unsigned char *skip;   // device, per group (one-mesh batches), may be NULL: groups to leave out

@@ -452,6 +452,7 @@ struct bz_batch_s {
     // batched FP32 mode with several meshes: one convolution launch for all of them (NULL: one per mesh)
     int4 *d_multi_items = nullptr;
     int n_multi_items = 0;
+    bz::MultiQueues queues{};
     bz::MeshConvDesc *d_desc = nullptr;   // per mesh, uploaded by bz_batch_set_weights
     size_t ws_mcounter = 0;
     bool per_mesh_now = false;       // one launch per mesh in place of the one-launch queue (autotuner)
@@ -969,14 +970,57 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         };
         std::stable_sort(conv.begin(), conv.end(), [&](const int4 &x, const int4 &y) { return cost(x) > cost(y); });
         std::stable_sort(core.begin(), core.end(), [](const int4 &x, const int4 &y) { return x.w - x.z > y.w - y.z; });
-        const size_t span = (conv.size() * kCoreSpreadNum) / kCoreSpreadDen;
-        size_t ci = 0;
-        for (size_t i = 0; i < conv.size(); ++i) {
-            // core items due before FP32 item i: ceil(i * ncore / span)
-            while (ci < core.size() && (span == 0 || ci * span < i * core.size())) mitems.push_back(core[ci++]);
-            mitems.push_back(conv[i]);
+        // queue of every item: the groups of all meshes in a line, each as long as its FP32 cost, cut into
+        // kMultiQueues equal lengths; a group's items, longest first, go to that one of its queues with
+        // the most of its length left.  From three groups on (Strang step of 256 N = 24 cells, 4 groups, 2.77
+        // -> 2.71 ms; the uneven batch 13.10 -> 12.94; with two, 72 N = 24 cells, the pops of empty queues
+        // at the end cost more, 1.03 -> 1.07 ms)
+        std::vector<int> first(b->parts.size() + 1, 0);
+        for (size_t mi = 0; mi < b->parts.size(); ++mi) first[mi + 1] = first[mi] + b->parts[mi].groups;
+        const int ng = first.back();
+        const int nq = ng >= 3 ? kMultiQueues : 1;
+        auto gid = [&](const int4 &x) { return first[(x.y >> 24) & 0xf] + x.x; };
+        std::vector<double> len(ng, 0.0);
+        double total = 0.0;
+        for (const int4 &x : conv) {
+            len[gid(x)] += (double)cost(x);
+            total += (double)cost(x);
         }
-        while (ci < core.size()) mitems.push_back(core[ci++]);
+        std::vector<std::vector<double>> left(ng, std::vector<double>(nq, 0.0));
+        double at = 0.0;
+        for (int g = 0; g < ng; ++g) {
+            for (int q = 0; q < nq; ++q)
+                left[g][q] = std::max(0.0, std::min(at + len[g], total * (q + 1) / nq) - std::max(at, total * q / nq));
+            at += len[g];
+        }
+        std::vector<std::vector<double>> core_left = left;
+        auto deal = [&](std::vector<double> &l, double c) {
+            const int q = (int)(std::max_element(l.begin(), l.end()) - l.begin());
+            l[q] -= c;
+            return q;
+        };
+        std::vector<double> core_len(ng, 0.0);
+        for (const int4 &x : core) core_len[gid(x)] += (double)(x.w - x.z);
+        std::vector<std::vector<int4>> qconv(nq), qcore(nq);
+        for (const int4 &x : conv) qconv[deal(left[gid(x)], (double)cost(x))].push_back(x);
+        for (const int4 &x : core) {
+            const int g = gid(x);
+            qcore[deal(core_left[g], (double)(x.w - x.z) * len[g] / std::max(1.0, core_len[g]))].push_back(x);
+        }
+        b->queues.n = nq;
+        for (int q = 0; q < nq; ++q) {
+            b->queues.start[q] = (int)mitems.size();
+            const size_t span = (qconv[q].size() * kCoreSpreadNum) / kCoreSpreadDen;
+            size_t ci = 0;
+            for (size_t i = 0; i < qconv[q].size(); ++i) {
+                // core items due before FP32 item i: ceil(i * ncore / span)
+                while (ci < qcore[q].size() && (span == 0 || ci * span < i * qcore[q].size()))
+                    mitems.push_back(qcore[q][ci++]);
+                mitems.push_back(qconv[q][i]);
+            }
+            while (ci < qcore[q].size()) mitems.push_back(qcore[q][ci++]);
+        }
+        b->queues.start[nq] = (int)mitems.size();
         o_multi = put(mitems.data(), mitems.size() * sizeof(int4));
         std::vector<MeshConvDesc> zero(b->parts.size());
         o_desc = put(zero.data(), zero.size() * sizeof(MeshConvDesc));
@@ -1438,7 +1482,7 @@ static bz_status collide_batched(bz_batch b, const double *d_f, double *d_Qt, ch
     }
     if (cores) BZ_HIP(hipEventRecord(b->ev_cjoin, b->core_stream), "core join");
     if (merged) {
-        const MultiLaunch ml{b->d_multi_items, b->n_multi_items, (unsigned *)(ws + b->ws_mcounter), b->d_desc, ws,
+        const MultiLaunch ml{b->d_multi_items, b->n_multi_items, b->queues, (unsigned *)(ws + b->ws_mcounter), b->d_desc, ws,
                              skip};
         std::pair<hipEvent_t, hipEvent_t> ev{};
         if (b->timing) {
