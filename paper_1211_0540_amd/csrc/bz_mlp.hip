@@ -43,7 +43,7 @@ __device__ inline float gelu_prime(float z) {
     return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.3989422804014327f;
 }
 
-enum { EPI_F32 = 0, EPI_GELU = 1, EPI_PARTIAL = 2 };
+enum { EPI_F32 = 0, EPI_GELU = 1, EPI_PARTIAL = 2, EPI_DGELU = 3 };
 
 constexpr int TBM = 128, TBN = 128, TBK = 32;
 constexpr int kXcds = 8;   // accelerator complex dies of the chip, each with its own L2
@@ -92,7 +92,9 @@ __device__ __forceinline__ void gemm_epilogue(const f32x4 (&acc)[4][4], int M, i
                     continue;
                 }
                 const float z = alpha * acc[i][j][r] + bcol;
-                if (EPI == EPI_GELU) {
+                if (EPI == EPI_DGELU) {
+                    Cbf[(size_t)row * ldcb + col] = f2bf(z * gelu_prime(C32[(size_t)row * ldc + col]));
+                } else if (EPI == EPI_GELU) {
                     C32[(size_t)row * ldc + col] = z;
                     Cbf[(size_t)row * ldcb + col] = f2bf(gelu(z));
                 } else {
@@ -117,6 +119,7 @@ __device__ __forceinline__ int lds_slot(int row, int c) { return c ^ ((row >> 2)
 
 // EPI_F32:  C32[m][n] = alpha * acc + (bias ? bias[n] : 0)
 // EPI_GELU: Z = acc + bias[n]; C32 = Z; Cbf = bf16(gelu(Z))
+// EPI_DGELU: Cbf = bf16(alpha * acc * gelu'(C32[m][n])), the gradient through the GELU whose input is C32
 // EPI_PARTIAL (split K): workgroup z of gridDim.z sums the k tiles
 //           [z nk / Z, (z + 1) nk / Z) and writes its raw sums to C32 + z M ldc;
 //           k_splitk_reduce then adds the Z slices in order and applies the epilogue.
@@ -214,6 +217,10 @@ __global__ void __launch_bounds__(256) k_splitk_reduce(int M, int N, int Z, cons
         float acc = 0.f;
         for (int z = 0; z < Z; ++z) acc += P[z * MN + i];
         const float v = alpha * acc + (bias ? bias[col] : 0.f);
+        if (EPI == EPI_DGELU) {
+            Cbf[(size_t)row * ldcb + col] = f2bf(v * gelu_prime(C32[(size_t)row * ldc + col]));
+            continue;
+        }
         C32[(size_t)row * ldc + col] = v;
         if (EPI == EPI_GELU) Cbf[(size_t)row * ldcb + col] = f2bf(gelu(v));
     }
@@ -307,28 +314,22 @@ __global__ void __launch_bounds__(256) k_sum_parts(int n, const double *__restri
     if (threadIdx.x == 0) loss[0] = (float)((red[0] + red[1] + red[2] + red[3]) * inv_n);
 }
 
-// dZ = bf16(dA * gelu'(Z))
-__global__ void k_gelu_bwd(size_t n, const float *__restrict__ dA, const float *__restrict__ Z,
-                           unsigned short *__restrict__ dZ) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        dZ[i] = f2bf(dA[i] * gelu_prime(Z[i]));
-}
-
-// db[n] = alpha * sum_m bf2f(D[m][n])  (D is rows x cols BF16).  A block of 64 x 16
-// threads owns 64 columns; thread (c, t) sums the rows r = t (mod 16) of its column,
-// then the 16 partial sums are added in order.
 // db[c] = alpha * sum over rows of D[r][c] (BF16 [rows][cols], cols a multiple of 8, 16-byte
-// aligned rows).  A block of 128 threads sums 64 columns: thread (tr, q) adds columns
-// 8q .. 8q + 7 of the rows tr, tr + 16, ... (one 16-byte load per row; 8 threads read 128
-// contiguous bytes of a row), then the 16 row-group partials are added in order.
-__global__ void __launch_bounds__(128) k_col_sums(int rows, int cols, const unsigned short *__restrict__ D,
+// aligned rows).  A block sums 64 columns: thread (tr, q) adds columns 8q .. 8q + 7 of the rows
+// tr, tr + kColRows, ... (one 16-byte load per row; 8 threads read 128 contiguous bytes of a row), then
+// the kColRows row-group partials are added in order, eight columns' worth at a time.  A hidden layer
+// has 16 blocks of columns, so a thread's chain of loads is what the kernel takes: 64 row groups
+// (512 rows: 8 loads) against 16 took 4 instead of 12 us.
+constexpr int kColRows = 64;
+__global__ void __launch_bounds__(8 * kColRows) k_col_sums(int rows, int cols, const unsigned short *__restrict__ D,
                                                   float alpha, float *__restrict__ db) {
-    __shared__ float part[16][64];
+    __shared__ float part[kColRows][64];
     const int tc = (threadIdx.x & 7) * 8, tr = threadIdx.x >> 3;
     const int c = blockIdx.x * 64 + tc;
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (c < cols)
-        for (int r = tr; r < rows; r += 16) {
+#pragma unroll 4
+        for (int r = tr; r < rows; r += kColRows) {
             const uint4 u = *(const uint4 *)(D + (size_t)r * cols + c);
             const unsigned w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
@@ -340,12 +341,20 @@ __global__ void __launch_bounds__(128) k_col_sums(int rows, int cols, const unsi
 #pragma unroll
     for (int k = 0; k < 8; ++k) part[tr][tc + k] = s[k];
     __syncthreads();
+    // eight threads per column add eight row groups each, then their sums are added in order
+    __shared__ float sub[8][64];
+    const int col = threadIdx.x & 63, oct = threadIdx.x >> 6;
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < kColRows / 8; ++i) t += part[oct * (kColRows / 8) + i][col];
+    sub[oct][col] = t;
+    __syncthreads();
     const int cc = blockIdx.x * 64 + threadIdx.x;
     if (threadIdx.x < 64 && cc < cols) {
-        float t = 0.f;
+        float v = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) t += part[i][threadIdx.x];
-        db[cc] = alpha * t;
+        for (int i = 0; i < 8; ++i) v += sub[i][threadIdx.x];
+        db[cc] = alpha * v;
     }
 }
 
@@ -457,7 +466,7 @@ constexpr int kMaxSplit = 16;
 struct WorkView {
     float *split;                // split-K slices
     size_t split_floats;
-    float *Z1, *Z2, *Y, *dA;     // FP32
+    float *Z1, *Z2, *Y;          // FP32
     unsigned short *A1, *A2;     // BF16 activations
     unsigned short *dY, *dZ;     // BF16 gradients (dZ reused for layers 2 and 1)
     unsigned short *tA, *tB;     // transposes
@@ -479,7 +488,6 @@ static WorkView work_view(const bz_mlp_s *n, int B, void *w) {
     v.Z1 = (float *)take((size_t)B * H * 4);
     v.Z2 = (float *)take((size_t)B * H * 4);
     v.Y = (float *)take((size_t)B * O * 4);
-    v.dA = (float *)take((size_t)B * H * 4);
     v.A1 = (unsigned short *)take((size_t)B * H * 2);
     v.A2 = (unsigned short *)take((size_t)B * H * 2);
     v.dY = (unsigned short *)take((size_t)B * O * 2);
@@ -494,7 +502,7 @@ static WorkView work_view(const bz_mlp_s *n, int B, void *w) {
 
 static size_t work_bytes(const bz_mlp_s *n, int B) {
     const size_t H = n->n_hid, O = n->n_out, I = n->n_in;
-    return a256((size_t)kMaxSplit * B * H * 4) + a256((size_t)B * H * 4) * 3 + a256((size_t)B * O * 4) +
+    return a256((size_t)kMaxSplit * B * H * 4) + a256((size_t)B * H * 4) * 2 + a256((size_t)B * O * 4) +
            a256((size_t)B * H * 2) * 3 +
            a256((size_t)B * O * 2) + 2 * a256(std::max(std::max(O, I), H) * (size_t)B * 2) + a256(16384 * 8) + 256;
 }
@@ -519,7 +527,10 @@ static hipError_t gemm(int epi, int M, int N, int K, const unsigned short *A, in
                            wv.split, N, nullptr, 0);
         const size_t mn = (size_t)M * N;
         const unsigned rg = (unsigned)std::min<size_t>((mn + 255) / 256, 4096);
-        if (epi == EPI_GELU)
+        if (epi == EPI_DGELU)
+            hipLaunchKernelGGL(k_splitk_reduce<EPI_DGELU>, dim3(rg), dim3(256), 0, s, M, N, split, wv.split, alpha, bias,
+                               C32, ldc, Cbf, ldcb);
+        else if (epi == EPI_GELU)
             hipLaunchKernelGGL(k_splitk_reduce<EPI_GELU>, dim3(rg), dim3(256), 0, s, M, N, split, wv.split, alpha, bias,
                                C32, ldc, Cbf, ldcb);
         else
@@ -527,7 +538,10 @@ static hipError_t gemm(int epi, int M, int N, int K, const unsigned short *A, in
                                C32, ldc, Cbf, ldcb);
         return hipGetLastError();
     }
-    if (epi == EPI_GELU)
+    if (epi == EPI_DGELU)
+        hipLaunchKernelGGL(k_gemm_nt<EPI_DGELU>, grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, alpha, bias, C32, ldc,
+                           Cbf, ldcb);
+    else if (epi == EPI_GELU)
         hipLaunchKernelGGL(k_gemm_nt<EPI_GELU>, grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, alpha, bias, C32, ldc,
                            Cbf, ldcb);
     else
@@ -548,7 +562,7 @@ static hipError_t transpose(int R, int C, const unsigned short *in, unsigned sho
 
 static hipError_t col_sums(int rows, int cols, const unsigned short *D, float alpha, float *db, hipStream_t s) {
     if (cols % 8 || (uintptr_t)D % 16) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_col_sums, dim3((cols + 63) / 64), dim3(128), 0, s, rows, cols, D, alpha, db);
+    hipLaunchKernelGGL(k_col_sums, dim3((cols + 63) / 64), dim3(8 * kColRows), 0, s, rows, cols, D, alpha, db);
     return hipGetLastError();
 }
 
@@ -594,20 +608,19 @@ static hipError_t backward(const bz_mlp_s *n, const ParamView &pv, const unsigne
     if (e == hipSuccess) e = transpose(B, H, wv.A2, wv.tB, s);
     if (e == hipSuccess) e = gemm(EPI_F32, O, H, B, wv.tA, B, wv.tB, B, gs, nullptr, g + n->oW3, H, nullptr, 0, wv, s);
     if (e == hipSuccess) e = col_sums(B, O, wv.dY, gs, g + n->ob3, s);
-    if (e == hipSuccess) e = gemm(EPI_F32, B, H, O, wv.dY, O, pv.W3t, O, gs, nullptr, wv.dA, H, nullptr, 0, wv, s);
-    hipLaunchKernelGGL(k_gelu_bwd, dim3(grid1((size_t)B * H)), dim3(256), 0, s, (size_t)B * H, wv.dA, wv.Z2, wv.dZ);
+    if (e == hipSuccess) e = gemm(EPI_DGELU, B, H, O, wv.dY, O, pv.W3t, O, gs, nullptr, wv.Z2, H, wv.dZ, H, wv, s);
     // layer 2 (dZ holds the true gradient dL/dZ2)
     if (e == hipSuccess) e = transpose(B, H, wv.dZ, wv.tA, s);
     if (e == hipSuccess) e = transpose(B, H, wv.A1, wv.tB, s);
     if (e == hipSuccess) e = gemm(EPI_F32, H, H, B, wv.tA, B, wv.tB, B, 1.f, nullptr, g + n->oW2, H, nullptr, 0, wv, s);
     if (e == hipSuccess) e = col_sums(B, H, wv.dZ, 1.f, g + n->ob2, s);
-    if (e == hipSuccess) e = gemm(EPI_F32, B, H, H, wv.dZ, H, pv.W2t, H, 1.f, nullptr, wv.dA, H, nullptr, 0, wv, s);
-    hipLaunchKernelGGL(k_gelu_bwd, dim3(grid1((size_t)B * H)), dim3(256), 0, s, (size_t)B * H, wv.dA, wv.Z1, wv.dZ);
+    // (into the activation buffer A2, read for dW3 and no longer needed: dZ is still an operand)
+    if (e == hipSuccess) e = gemm(EPI_DGELU, B, H, H, wv.dZ, H, pv.W2t, H, 1.f, nullptr, wv.Z1, H, wv.A2, H, wv, s);
     // layer 1
-    if (e == hipSuccess) e = transpose(B, H, wv.dZ, wv.tA, s);
+    if (e == hipSuccess) e = transpose(B, H, wv.A2, wv.tA, s);
     if (e == hipSuccess) e = transpose(B, I, X, wv.tB, s);
     if (e == hipSuccess) e = gemm(EPI_F32, H, I, B, wv.tA, B, wv.tB, B, 1.f, nullptr, g + n->oW1, I, nullptr, 0, wv, s);
-    if (e == hipSuccess) e = col_sums(B, H, wv.dZ, 1.f, g + n->ob1, s);
+    if (e == hipSuccess) e = col_sums(B, H, wv.A2, 1.f, g + n->ob1, s);
     return e == hipSuccess ? hipGetLastError() : e;
 }
 
