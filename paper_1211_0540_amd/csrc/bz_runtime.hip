@@ -951,24 +951,27 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
                        b->parts.size() <= (size_t)kMaxMultiMeshes && !(flags & BZ_BATCH_PER_MESH);
     std::vector<int4> mitems;
     if (multi) {
-        std::vector<int4> conv, core;
+        struct Costed {
+            long long cost;
+            int4 it;
+        };
+        std::vector<Costed> conv;
+        std::vector<int4> core;
         for (size_t mi = 0; mi < b->parts.size(); ++mi) {
-            for (int4 it : b->parts[mi].h_items) {
+            const Part &p = b->parts[mi];
+            const long long step = pairs_per_step(p.g->N);
+            for (int4 it : p.h_items) {
                 it.y |= (int)mi << 24;
-                conv.push_back(it);
+                // a narrow group takes 64 / W steps at once
+                const int sh = it.x == p.tail.g ? 6 - p.tail.lw : 0;
+                conv.push_back({((it.w - it.z + (1 << sh) - 1) >> sh) * step, it});
             }
-            for (int4 it : b->parts[mi].h_core_items) {
+            for (int4 it : p.h_core_items) {
                 it.y |= ((int)mi << 24) | kCoreItemBit;
                 core.push_back(it);
             }
         }
-        auto cost = [&](const int4 &x) {
-            const Part &p = b->parts[(x.y >> 24) & 0xf];
-            // a narrow group takes kWave / W steps at once
-            const int S = x.x == p.tail.g ? kWave >> p.tail.lw : 1;
-            return (long long)((x.w - x.z + S - 1) / S) * pairs_per_step(p.g->N);
-        };
-        std::stable_sort(conv.begin(), conv.end(), [&](const int4 &x, const int4 &y) { return cost(x) > cost(y); });
+        std::stable_sort(conv.begin(), conv.end(), [](const Costed &x, const Costed &y) { return x.cost > y.cost; });
         std::stable_sort(core.begin(), core.end(), [](const int4 &x, const int4 &y) { return x.w - x.z > y.w - y.z; });
         // queue of every item: the groups of all meshes in a line, each as long as its FP32 cost, cut into
         // kMultiQueues equal lengths; a group's items, longest first, go to that one of its queues with
@@ -982,9 +985,9 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         auto gid = [&](const int4 &x) { return first[(x.y >> 24) & 0xf] + x.x; };
         std::vector<double> len(ng, 0.0);
         double total = 0.0;
-        for (const int4 &x : conv) {
-            len[gid(x)] += (double)cost(x);
-            total += (double)cost(x);
+        for (const Costed &x : conv) {
+            len[gid(x.it)] += (double)x.cost;
+            total += (double)x.cost;
         }
         std::vector<std::vector<double>> left(ng, std::vector<double>(nq, 0.0));
         double at = 0.0;
@@ -1002,7 +1005,7 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         std::vector<double> core_len(ng, 0.0);
         for (const int4 &x : core) core_len[gid(x)] += (double)(x.w - x.z);
         std::vector<std::vector<int4>> qconv(nq), qcore(nq);
-        for (const int4 &x : conv) qconv[deal(left[gid(x)], (double)cost(x))].push_back(x);
+        for (const Costed &x : conv) qconv[deal(left[gid(x.it)], (double)x.cost)].push_back(x.it);
         for (const int4 &x : core) {
             const int g = gid(x);
             qcore[deal(core_left[g], (double)(x.w - x.z) * len[g] / std::max(1.0, core_len[g]))].push_back(x);
