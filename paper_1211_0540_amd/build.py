@@ -11,7 +11,9 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbz.so")
-SOURCES = ["bz_runtime.hip", "bz_dft.hip", "bz_misc.hip", "bz_conv.hip", "bz_transport.hip", "bz_mlp.hip", "bz_surrogate.hip"]
+# (source, object, defines), longest first; the convolution kernels compile in four units
+UNITS = [("bz_conv.hip", f"bz_conv{u}.o", [f"-DBZ_CONV_UNIT={u}"]) for u in (0, 2, 3, 1)]
+UNITS += [(f"bz_{n}.hip", f"bz_{n}.o", []) for n in ("dft", "runtime", "surrogate", "misc", "mlp", "transport")]
 ARCH = os.environ.get("BZ_OFFLOAD_ARCH", "gfx950")
 
 
@@ -21,13 +23,13 @@ def hipcc_flags():
             "-Wno-unused-command-line-argument", "-I", os.path.join(HERE, "..", "include")]
 
 
-def build(verbose: bool = False, jobs: int = 4) -> str:
+def build(verbose: bool = False, jobs: int = 10) -> str:
     objs = []
     procs = []
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
-    for src in SOURCES:
-        obj = os.path.join(HERE, "_build", src.replace(".hip", ".o"))
-        cmd = ["hipcc", *hipcc_flags(), "-c", os.path.join(CSRC, src), "-o", obj]
+    for src, name, defs in UNITS:
+        obj = os.path.join(HERE, "_build", name)
+        cmd = ["hipcc", *hipcc_flags(), *defs, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((subprocess.Popen(cmd), src))

@@ -20,8 +20,8 @@
 //   operations per visited pair: 4 for the complex product fhat_m fhat_j and 2
 //   FMAs that add its weighted parts to a fresh per-output partial of the step,
 //   plus 2 additions per output and step into the running sums (and 2 more that
-//   combine two interleaved partials, where a variant keeps two).  Work items are popped from an atomic
-//   queue ordered longest first, so the launch is persistent.  Every item names
+//   combine two interleaved partials, where a variant keeps two).  Work items are popped from
+//   atomic queues ordered longest first, so the launch is persistent.  Every item names
 //   its pass of the conjugate-symmetric schedule (bz_internal.h): which fhat
 //   copy it reads, which weight stream and which output buffer it writes; the
 //   full-sum schedule uses pass A only.  Steps of pass A whose rows lie on a
@@ -45,6 +45,13 @@
 #include <utility>
 
 #include "bz_internal.h"
+
+// The file is compiled in four units side by side (BZ_CONV_UNIT): 0 the one launch, the cores and the
+// dispatch, 1 and 2 the per-mesh FP32 variants of the small and large meshes, 3 FP64 and plain; in
+// one unit it takes ten minutes.
+#ifndef BZ_CONV_UNIT
+#error "compile with -DBZ_CONV_UNIT=0 .. 3"
+#endif
 
 namespace bz {
 namespace {
@@ -776,6 +783,7 @@ __device__ __forceinline__ void multi_core(const MeshConvDesc &d, char *ws, cons
         core_item<R>(d.N, d.nD, cf, d.core_steps, d.core_ext, d.core_w, out, d.cq_pstride, item, wl);
 }
 
+#if BZ_CONV_UNIT == 0
 // The work queues of the one launch (MultiQueues): a wavefront takes items from its XCD's queue, then
 // from the others in turn.
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
@@ -823,6 +831,7 @@ k_conv_cells_f32_multi(const int4 *__restrict__ items, const MultiQueues mq, uns
         }
     }
 }
+#endif
 
 // ---------------------------------------------------------------------------
 // Batched FP64.
@@ -1052,6 +1061,7 @@ hipError_t plain_launch(const PlainLaunch &p, hipStream_t s) {
 
 }  // namespace
 
+#if BZ_CONV_UNIT == 0
 int conv_variant_count() { return (int)(sizeof(kVariantAcc) / sizeof(kVariantAcc[0])); }
 
 // The compensation form does not enter the rank: the FP64 total (in registers or in the
@@ -1110,16 +1120,45 @@ hipError_t launch_conv_core(const CoreLaunch &p, hipStream_t s) {
     }
 }
 
-#define BZ_FOR_EACH_N(X) X(8) X(12) X(16) X(20) X(24) X(28) X(32)
-
 hipError_t launch_conv_cells(const CellsLaunch &p, bool f64, hipStream_t s) {
     if (p.n_items <= 0) return hipSuccess;
     hipError_t e = launch_fill_u32(p.counter, 1, 0u, s);
     if (e != hipSuccess) return e;
     const unsigned grid = persistent_grid(p.n_items);
-#define CASE(NN)                                                                                   \
-    case NN:                                                                                       \
-        return f64 ? cells_f64_launch<NN>(p, grid, s) : cells_f32_variant<NN>(p, grid, s);
+    if (f64) return launch_cells_f64(p, grid, s);
+    return p.N <= 20 ? launch_cells_f32_small(p, grid, s) : launch_cells_f32_large(p, grid, s);
+}
+#endif
+
+#if BZ_CONV_UNIT == 1
+hipError_t launch_cells_f32_small(const CellsLaunch &p, unsigned grid, hipStream_t s) {
+    switch (p.N) {
+    case 8: return cells_f32_variant<8>(p, grid, s);
+    case 12: return cells_f32_variant<12>(p, grid, s);
+    case 16: return cells_f32_variant<16>(p, grid, s);
+    case 20: return cells_f32_variant<20>(p, grid, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+#endif
+
+#if BZ_CONV_UNIT == 2
+hipError_t launch_cells_f32_large(const CellsLaunch &p, unsigned grid, hipStream_t s) {
+    switch (p.N) {
+    case 24: return cells_f32_variant<24>(p, grid, s);
+    case 28: return cells_f32_variant<28>(p, grid, s);
+    case 32: return cells_f32_variant<32>(p, grid, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+#endif
+
+#if BZ_CONV_UNIT == 3
+#define BZ_FOR_EACH_N(X) X(8) X(12) X(16) X(20) X(24) X(28) X(32)
+
+hipError_t launch_cells_f64(const CellsLaunch &p, unsigned grid, hipStream_t s) {
+#define CASE(NN) \
+    case NN: return cells_f64_launch<NN>(p, grid, s);
     switch (p.N) {
         BZ_FOR_EACH_N(CASE)
     default:
@@ -1139,5 +1178,6 @@ hipError_t launch_conv_plain(const PlainLaunch &p, bool f64, hipStream_t s) {
     }
 #undef CASE
 }
+#endif
 
 }  // namespace bz

@@ -418,6 +418,10 @@ hipError_t launch_build_e3(int N, const long long *d_row_woff, const long long *
 int conv_variant_count();
 int conv_variant_accuracy_rank(int v);
 hipError_t launch_conv_cells(const CellsLaunch &p, bool f64, hipStream_t s);
+// its kernels, in compilation units of their own: FP32 variants for N <= 20 and above, FP64
+hipError_t launch_cells_f32_small(const CellsLaunch &p, unsigned grid, hipStream_t s);
+hipError_t launch_cells_f32_large(const CellsLaunch &p, unsigned grid, hipStream_t s);
+hipError_t launch_cells_f64(const CellsLaunch &p, unsigned grid, hipStream_t s);
 
 // FP64 core sum of one mesh (CoreSched): items (group, output row | kind << 16 | piece << 20, first
 // step, end step), longest first; kind 2 writes the outputs k3 - N/2 in [-2r, 2r], kind 0 those in
