@@ -16,7 +16,7 @@ The JSON line also carries:
                 visits, per cell.  The full sum's algorithmic flops over the same
                 time are reported apart as `effective_tflops` (never in `frac`);
                 so are the FP64 core's flops and the issue ceiling of the kernel's
-                instruction mix without packed FP32.
+                instruction mix.
   cpu_baseline  the FP64 CPU oracle on a bounded sample of the same cells
   comparisons   the plain unbatched and the batched FP64 paths on the same GPU,
                 the relative L2 error of every cell against the plain FP64
@@ -36,10 +36,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "cell-collision evals/s at N=32: FP32 batched & surrogate vs FP64 plain; rel L2 err"
-PEAK_FP32_TFLOPS = 157.3   # MI355X FP32 vector, published (packed FP32: two lanes' FMAs per instruction)
-# Without packed FP32 one FMA per lane issues per 4 cycles per SIMD (78.6 TFLOP/s, half the peak);
-# the kernel's 4 FMA + 2 MUL per slot carry 10 flops in 6 instructions: 0.5 * 10 / 12 of the peak.
-ISSUE_CEILING_FRAC = 0.5 * 10.0 / 12.0
+PEAK_FP32_TFLOPS = 157.3   # MI355X FP32 vector, published
+# Two wavefronts of a SIMD together issue one wave64 FP32 instruction per 2 cycles (one alone, one per
+# 4), which is the published rate; the kernel's 4 FMA + 2 MUL per slot carry 10 flops in 6
+# instructions, 10 / 12 of the peak.
+ISSUE_CEILING_FRAC = 10.0 / 12.0
 TRAIN_STEPS = 30000        # closure training: Adam steps of 512 rows
 HBM_TBPS = 8.0
 
@@ -93,7 +94,7 @@ def core_products(N, r2):
     """Complex products per cell and evaluation of the FP64 core (r2 = 0: none): for every
     output row (k1, k2) within 2r of the centre, the pairs of disk rows m <= j with
     m + j = k + N/2 (the core steps), each the products of the two rows' entries inside the
-    ball (a row at distance rho from the centre has 2 floor(sqrt(r2 - rho^2)) + 1 of them), of
+    ball (the kernel leaves out j values two at a time, so it executes a few more) (a row at distance rho from the centre has 2 floor(sqrt(r2 - rho^2)) + 1 of them), of
     all outputs, or of the outputs k3 <= N/2 on the derived rows of the conjugate-symmetric
     schedule, which are skipped when 2r < N/2."""
     if r2 < 1:
@@ -783,9 +784,9 @@ def main():
                      "traffic_gb_per_s": (traffic / (conv_avg_ms * 1e-3) / 1e9) if traffic else None,
                      "hbm_peak_gb_per_s": HBM_TBPS * 1e3,
                      "valu_insts_per_launch": valu,
-                     # one wave64 VALU instruction per SIMD every 4 cycles (1024 SIMDs): the mean shader
+                     # one wave64 VALU instruction per SIMD every 2 cycles (1024 SIMDs): the mean shader
                      # clock the launch needs at least to issue them in its measured time
-                     "valu_issue_clock_ghz_min": (valu / 1024 * 4 / (conv_avg_ms * 1e-3) / 1e9) if valu else None},
+                     "valu_issue_clock_ghz_min": (valu / 1024 * 2 / (conv_avg_ms * 1e-3) / 1e9) if valu else None},
         "cpu_baseline": cpu,
         "gpu_clock_idle_after_run": gpu_clocks(),
         "comparisons": comp,

@@ -216,12 +216,14 @@ bz_status bz_batch_create(int n_cells, const int32_t *grid_of_cell, int n_grids,
  *                      second stream of the batch.  By default a batch of up
  *                      to four meshes, or of one mesh with an FP64 core, runs
  *                      the work items of all meshes and all cores in one
- *                      persistent launch from one queue: the FP32 items
+ *                      persistent launch from one queue (from three 64-cell
+ *                      groups on, one per XCD): the FP32 items
  *                      ordered by cost, each naming its mesh (the variant
  *                      with FOLD 16 and two interleaved partials for every
  *                      mesh), and the FP64 core items spread through the
- *                      first 3/5 of it; the transforms stay one launch per
- *                      mesh and pass.  bz_batch_autotune may switch a batch
+ *                      first 3/5 of it; a last group of at most 32 cells takes
+ *                      several steps at once, with bitwise the same results;
+ *                      the transforms stay one launch per mesh and pass.  bz_batch_autotune may switch a batch
  *                      to the per-mesh launches when they are faster.
  *   BZ_BATCH_FINE_SPLIT  cut the rows into work items small enough for the
  *                      rows of a single 64-cell group to fill the device (by
