@@ -94,8 +94,8 @@ def core_products(N, r2):
     """Complex products per cell and evaluation of the FP64 core (r2 = 0: none): for every
     output row (k1, k2) within 2r of the centre, the pairs of disk rows m <= j with
     m + j = k + N/2 (the core steps), each the products of the two rows' entries inside the
-    ball (the kernel leaves out j values two at a time, so it executes a few more) (a row at distance rho from the centre has 2 floor(sqrt(r2 - rho^2)) + 1 of them), of
-    all outputs, or of the outputs k3 <= N/2 on the derived rows of the conjugate-symmetric
+    ball (a row at distance rho from the centre has 2 floor(sqrt(r2 - rho^2)) + 1 of them; the
+    kernel leaves out j values two at a time, so it executes a few more), of all outputs, or of the outputs k3 <= N/2 on the derived rows of the conjugate-symmetric
     schedule, which are skipped when 2r < N/2."""
     if r2 < 1:
         return 0

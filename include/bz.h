@@ -216,8 +216,9 @@ bz_status bz_batch_create(int n_cells, const int32_t *grid_of_cell, int n_grids,
  *                      second stream of the batch.  By default a batch of up
  *                      to four meshes, or of one mesh with an FP64 core, runs
  *                      the work items of all meshes and all cores in one
- *                      persistent launch from one queue (from three 64-cell
- *                      groups on, one per XCD): the FP32 items
+ *                      persistent launch from one queue (large batches, of
+ *                      13 MB of fhat and three groups on, from one per XCD):
+ *                      the FP32 items
  *                      ordered by cost, each naming its mesh (the variant
  *                      with FOLD 16 and two interleaved partials for every
  *                      mesh), and the FP64 core items spread through the

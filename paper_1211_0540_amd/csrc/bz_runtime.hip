@@ -975,13 +975,21 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         std::stable_sort(core.begin(), core.end(), [](const int4 &x, const int4 &y) { return x.w - x.z > y.w - y.z; });
         // queue of every item: the groups of all meshes in a line, each as long as its FP32 cost, cut into
         // kMultiQueues equal lengths; a group's items, longest first, go to that one of its queues with
-        // the most of its length left.  From three groups on (Strang step of 256 N = 24 cells, 4 groups, 2.77
-        // -> 2.71 ms; the uneven batch 13.10 -> 12.94; with two, 72 N = 24 cells, the pops of empty queues
-        // at the end cost more, 1.03 -> 1.07 ms)
+        // the most of its length left.  Queues pay where the fhat rows of the groups, a narrow one's by its
+        // lanes, are beyond what the L2s hold of them: from three groups and 13 MB on (one queue / eight,
+        // Strang steps: 256 N = 24 cells, 28 MB, 2.77 / 2.71 ms; 192 of N = 28, 34 MB, 4.61 / 4.46; 400 of N = 16,
+        // 13.1 MB, 0.93 / 0.90; the uneven batch 13.10 / 12.94 per Heun step).  Below, a wavefront's pops of
+        // seven empty queues at the end cost more: 192 of N = 20, 12.3 MB, 1.01 / 1.04; 158 of N = 12,
+        // 2.2 MB, 0.29 / 0.36; two groups, 72 of N = 24, 1.03 / 1.07
         std::vector<int> first(b->parts.size() + 1, 0);
         for (size_t mi = 0; mi < b->parts.size(); ++mi) first[mi + 1] = first[mi] + b->parts[mi].groups;
         const int ng = first.back();
-        const int nq = ng >= 3 ? kMultiQueues : 1;
+        double row_bytes = 0.0;
+        for (const Part &p : b->parts) {
+            const double lanes = p.tail.g >= 0 ? (p.groups - 1) * kWave + (1 << p.tail.lw) : p.groups * kWave;
+            row_bytes += lanes * 8.0 * p.g->N * p.g->N * p.g->N;
+        }
+        const int nq = ng >= 3 && row_bytes >= 13.0e6 ? kMultiQueues : 1;
         auto gid = [&](const int4 &x) { return first[(x.y >> 24) & 0xf] + x.x; };
         std::vector<double> len(ng, 0.0);
         double total = 0.0;

@@ -54,3 +54,23 @@ def test_narrow_groups_fp64_are_bitwise_the_wide_ones(dev, N, L, n):
         c.close()
     assert np.all(np.isfinite(out[0]))
     assert np.array_equal(out[0], out[1])
+
+
+# one queue and a queue per XCD (from three groups and 13 MB of fhat rows on): the smallest batch of N = 16
+# on the upper side of the line and one below it, a narrow last group, a batch of three groups
+@pytest.mark.parametrize("N,L,n", [(16, 6.0, 400), (16, 6.0, 330), (24, 7.0, 160), (28, 7.0, 129)])
+def test_queues_are_bitwise_the_per_mesh_launch(dev, N, L, n):
+    base = W.random_smooth_cells(20, N, L, seed=500 + N, umax=0.5)
+    cells = [base[i % 20] * (1.0 + i / 1024) for i in range(n)]
+    out = []
+    for per_mesh in (False, True):
+        c = bz.Collision([(N, L, 1.0)], [0] * n, "batched_f32", weights_cache=_WCACHE, per_mesh=per_mesh)
+        assert bz.bz_batch_one_launch(c.batch) != per_mesh
+        c.set_variant(12)
+        f = torch.from_numpy(c.pack(cells)).to(dev)
+        for _ in range(2):
+            out.append(c.collide(f).cpu().numpy())
+        c.close()
+    assert np.all(np.isfinite(out[0]))
+    for o in out[1:]:
+        assert np.array_equal(out[0], o)
