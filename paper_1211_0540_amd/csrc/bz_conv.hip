@@ -430,8 +430,11 @@ k_conv_cells_f32(const float2 *__restrict__ fh, const int4 *__restrict__ items, 
 // 16 bytes and lane (a step's weights are contiguous), kRing reads ahead of their use; that is
 // what bounds the pass: 16 cycles of the CU's L1 per 24 operations, as the broadcasts of LDS.
 // LDS: [N values][64 lanes] partials, [2N values][W cells] running sums (W <= 32).  FP64 items (one partial per output and step, no fold) take the same
-// form at half the read-ahead (one N = 32 cell: 1.1 against
+// form at half the read-ahead (one N = 32 cell: 0.97 against
 // 2.9 ms an evaluation).
+// REMAT: what is the same in every pass (LDS addresses, row strides) is computed again in each: kept
+// live it takes registers that the wide body of the same kernel is short of (FP64, N = 32: 16
+// cells 2.77 -> 2.34 ms an evaluation).
 template <typename T>
 constexpr int narrow_lds_bytes(int N) {
     return (int)sizeof(T) * N * (kWave + 2 * (kWave / 2));
@@ -446,9 +449,9 @@ template <>
 struct vec4<double> {
     using t = double4;
 };
-template <typename T, int N>
+template <typename T, int N, bool REMAT>
 __device__ __forceinline__ void narrow_item(const typename cplx<T>::t *fh, double2 *qh, const ConvPass &cp, const int4 item,
-                                            int lw, lds_char *lds, lds_char *sink) {
+                                            const int lw, lds_char *lds, lds_char *sink) {
     using C = typename cplx<T>::t;
     using T4 = typename vec4<T>::t;
     typedef __attribute__((address_space(3))) T lds_t;
@@ -456,7 +459,9 @@ __device__ __forceinline__ void narrow_item(const typename cplx<T>::t *fh, doubl
     constexpr int h = N / 2, M = N * N * N, PS = 3 * N * N / 4, FOLD = 16, kRing = f32 ? 14 : 7, SPLIT = f32 ? 2 : 1;
     constexpr int CB = (int)sizeof(C), CS = f32 ? 3 : 4;   // bytes of a complex value, and their log2
     const int W = 1 << lw, S = kWave >> lw;
-    const int lane = threadIdx.x, cell = lane & (W - 1), slice = lane >> lw;
+    int lane = threadIdx.x;
+    if constexpr (REMAT) asm volatile("" : "+v"(lane));
+    const int cell = lane & (W - 1), slice = lane >> lw;
     const int g = item.x, r = item.y & 0xffff, part = (item.y >> 16) & 0xf, s0 = item.z, s1 = item.w;
     const int k1 = r / N, k2 = r - k1 * N, lo2 = axis_lo(N, k2);
     double *const out = (double *)(qh + cp.out_off + part * cp.pstride + g * cp.gstride) +
@@ -484,6 +489,8 @@ __device__ __forceinline__ void narrow_item(const typename cplx<T>::t *fh, doubl
     bool first = true;
     for (int s = s0; s < s1; s += S) {
         const int left = s1 - s < S ? s1 - s : S;             // steps of this pass
+        int pl = lane, plw = lw;                              // this pass's copies
+        if constexpr (REMAT) asm volatile("" : "+v"(pl), "+s"(plw));
         const bool fold = (f32 && (s + S - s0) % FOLD == 0) || s + S >= s1;
         const unsigned um = (unsigned)((((m1 * N + m2) * N) << lw) + cell) * (unsigned)CB;
         const unsigned uj = (unsigned)(((((k1 + h - m1) * N + (k2 + h - m2)) * N) << lw) + cell) * (unsigned)CB;
@@ -491,8 +498,8 @@ __device__ __forceinline__ void narrow_item(const typename cplx<T>::t *fh, doubl
         C mv[N], jv[N];
 #pragma unroll
         for (int t = 0; t < N; ++t) {
-            mv[t] = *(const C *)(G + (t << (lw + CS)) + um);
-            jv[t] = *(const C *)(G + (t << (lw + CS)) + uj);
+            mv[t] = *(const C *)(G + (t << (plw + CS)) + um);
+            jv[t] = *(const C *)(G + (t << (plw + CS)) + uj);
         }
         if (s + S < s1) touch(s + S);
         T4 ring[kRing];
@@ -539,8 +546,8 @@ __device__ __forceinline__ void narrow_item(const typename cplx<T>::t *fh, doubl
             });
             // lane positions rotated by value, so that lanes reading different values hit different banks
             constexpr int v = 2 * (k3 % h);
-            part_l[v * kWave + (lane ^ ((v << lw) & (kWave - 1)))] = f32 ? sr[0] + sr[SPLIT - 1] : sr[0];
-            part_l[(v + 1) * kWave + (lane ^ (((v + 1) << lw) & (kWave - 1)))] = f32 ? si[0] + si[SPLIT - 1] : si[0];
+            part_l[v * kWave + (pl ^ ((v << plw) & (kWave - 1)))] = f32 ? sr[0] + sr[SPLIT - 1] : sr[0];
+            part_l[(v + 1) * kWave + (pl ^ (((v + 1) << plw) & (kWave - 1)))] = f32 ? si[0] + si[SPLIT - 1] : si[0];
             if constexpr (k3 % h == h - 1) flush(k3 / h);
         });
         if (fold) first = false;
@@ -767,7 +774,7 @@ template <int N>
 __device__ __forceinline__ void fp32_item(const MeshConvDesc &d, char *ws, int pass, const int4 item, lds_char *lds) {
     lds_char *const sink = lds + kMultiSink;
     if (item.x == d.tail_g)
-        narrow_item<float, N>((const float2 *)(ws + d.fh_bytes), (double2 *)(ws + d.qh_bytes), d.ps.p[pass], item, d.tail_lw, lds,
+        narrow_item<float, N, false>((const float2 *)(ws + d.fh_bytes), (double2 *)(ws + d.qh_bytes), d.ps.p[pass], item, d.tail_lw, lds,
                               sink);
     else
         multi_item<N>(d, ws, pass, item, lds, sink);
@@ -840,16 +847,25 @@ k_conv_cells_f32_multi(const int4 *__restrict__ items, const MultiQueues mq, uns
 // cells 2.76 -> 2.41 ms an evaluation): with one wavefront per SIMD the broadcast LDS reads take 32 cycles per
 // pair and CU, the FP64 operations of the four SIMDs 24.  Below, two or more wavefronts share a SIMD and the
 // wait for a chunk of 16 weights costs more (N = 20 1.06 against 1.12 ms, N = 16 330 against 352 us).
-template <int N>
-__global__ void __launch_bounds__(64) k_conv_cells_f64(const double2 *__restrict__ fh, const int4 *__restrict__ items,
-                                                       int n_items, unsigned *__restrict__ counter,
-                                                       double2 *__restrict__ qh,
-                                                       const unsigned char *__restrict__ skip, const ConvPasses ps,
-                                                       const NarrowTail nt) {
+// Forms of the kernel at N = 16, by the groups of the batch.  The wide body alone takes 250 of the 256 vector
+// registers that leave two wavefronts on a SIMD, with the narrow body beside it 290 (256 cells 321 against 365 us): a batch
+// of whole groups has a kernel without the narrow body.  With whole groups and a narrow one the two are
+// held to 256, at twelve spills outside the products (80 cells 168 -> 146 us, 270 395 -> 357); a narrow group alone
+// keeps its registers (32 cells 114 us, 129 at 256).  The other meshes have the mixed form alone: below, both
+// bodies fit (N = 12: 243; N = 8 times the same at 132 and 170), above, the wide body has one wavefront per SIMD anyway.
+enum { kMixedGroups = 0, kWholeGroups = 1, kNarrowGroup = 2 };
+__host__ __device__ constexpr int f64_form(int N, int form) { return N == 16 ? form : kMixedGroups; }
+template <int N, int FORM>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
+    N == 16 && FORM != kNarrowGroup ? 2 : 1, N == 16 && FORM == kNarrowGroup ? 1 : 8)))
+k_conv_cells_f64(const double2 *__restrict__ fh, const int4 *__restrict__ items, int n_items,
+                 unsigned *__restrict__ counter, double2 *__restrict__ qh, const unsigned char *__restrict__ skip,
+                 const ConvPasses ps, const NarrowTail nt) {
     constexpr int h = N / 2, M = N * N * N, PS = 3 * N * N / 4;
     constexpr bool kScalar = N >= 24;
     constexpr int CH = (PS * 8 + 1023) / 1024, CW = weight_chunk<double, N>(), WL = (PS * 8 + 4095) / 4096;
-    constexpr int kLds = 2 * CH * 1024 > narrow_lds_bytes<double>(N) ? 2 * CH * 1024 : narrow_lds_bytes<double>(N);
+    constexpr int kNarrowLds = FORM == kWholeGroups ? 0 : narrow_lds_bytes<double>(N);
+    constexpr int kLds = 2 * CH * 1024 > kNarrowLds ? 2 * CH * 1024 : kNarrowLds;
     __shared__ __attribute__((aligned(16))) double wbuf[(kLds + 256) / 8];
     lds_char *const wl = lds_ptr(&wbuf[0]), *const sink = wl + kLds;   // sink: written by the prefetches into L2
     const int lane = threadIdx.x;
@@ -867,8 +883,8 @@ __global__ void __launch_bounds__(64) k_conv_cells_f64(const double2 *__restrict
             for (int t = 0; t < N; ++t) out[t * kWave] = make_double2(0.0, 0.0);
             continue;
         }
-        if (g == nt.g) {
-            narrow_item<double, N>(fh, qh, cp, item, nt.lw, wl, sink);
+        if (FORM == kNarrowGroup || (FORM == kMixedGroups && g == nt.g)) {
+            narrow_item<double, N, (N >= 16 && FORM == kMixedGroups)>(fh, qh, cp, item, nt.lw, wl, sink);
             continue;
         }
         const double *w = (const double *)cp.w + cp.row_woff[r] + (long long)s0 * PS;
@@ -1046,8 +1062,14 @@ hipError_t cells_f32_variant(const CellsLaunch &p, unsigned grid, hipStream_t s)
 
 template <int N>
 hipError_t cells_f64_launch(const CellsLaunch &p, unsigned grid, hipStream_t s) {
-    hipLaunchKernelGGL((k_conv_cells_f64<N>), dim3(grid), dim3(64), 0, s, (const double2 *)p.fh, p.items,
-                       p.n_items, p.counter, p.qh, p.skip, p.passes, p.tail);
+    auto launch = [&](auto form) {
+        hipLaunchKernelGGL((k_conv_cells_f64<N, f64_form(N, form)>), dim3(grid), dim3(64), 0, s, (const double2 *)p.fh,
+                           p.items, p.n_items, p.counter, p.qh, p.skip, p.passes, p.tail);
+    };
+    // a narrow group is the last one: as group 0 it is the only one
+    if (p.tail.g < 0) launch(std::integral_constant<int, kWholeGroups>{});
+    else if (p.tail.g == 0) launch(std::integral_constant<int, kNarrowGroup>{});
+    else launch(std::integral_constant<int, kMixedGroups>{});
     return hipGetLastError();
 }
 
