@@ -769,9 +769,12 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         // a last group of at most 32 cells: W = 4, 8, 16 or 32 lanes hold its cells in the one launch
         // and the FP64 kernel, which take 64 / W steps of a row at once (FP32 items of one group, W = 64 / 32 / 4: N = 32
         // 1.41 / 1.24 / 0.30 ms, N = 24 345 / 286 / 104 us, N = 16 80 / 74 / 44 us; above 32 cells
-        // there is no second step to take)
+        // there is no second step to take).  In FP64 from N = 28 on W = 32 does not pay: two rows of a cell
+        // take half the registers or more, and two steps at once cost more than one after the other (32 cells
+        // narrow / wide: N = 28 2.06 / 1.80 ms, N = 32 4.34 / 2.93; 16 cells 1.21 / 1.80 and 2.34 / 2.93; N = 24 0.68 / 0.70)
         const int rest = (int)(p.cells.size() % kWave);
-        if (rest >= 1 && rest <= kWave / 2) {
+        const int most = mode == BZ_MODE_BATCHED_F64 && p.g->N >= 28 ? kWave / 4 : kWave / 2;
+        if (rest >= 1 && rest <= most) {
             p.tail.g = p.groups - 1;
             p.tail.lw = 2;
             while ((1 << p.tail.lw) < rest) ++p.tail.lw;
