@@ -1,6 +1,8 @@
 // Conservation projection (Sec. 3.3), Heun update helpers (Sec. 3.1) and the
 // expansion of the universal weight table into the schedules' weight streams
 // (Sec. 2.2 eq. GHat_calc).  FP64 throughout.
+#include <type_traits>
+
 #include "bz_internal.h"
 
 namespace bz {
@@ -253,15 +255,22 @@ __global__ void k_fill_u32(unsigned *p, int n, unsigned v) {
 // Diagnostics (Sec. 5: bulk velocity, marginal near the wall).  One block per
 // cell, fixed reduction order: density and bulk velocity in a first pass, the
 // temperature about that velocity in a second.  A cell is one block's work, so
-// what a thread waits for in turn sets the time: 1024 threads hold the cell in
+// what a thread waits for in turn sets the time: the block holds the cell in
 // registers over both passes (every load issued at once, N a template parameter),
-// and the second level of a sum is one LDS read and four shuffles (72 N = 24
-// cells and the wall marginal 25 -> 15 us against 256 threads that read the cell twice).
+// and the second level of a sum is a few LDS reads and shuffles.  A block has 256 threads
+// up to N = 16, 512 at N = 20 and 1024 above, which leaves 2 to 32 values to a thread
+// (72 N = 24 cells and the wall marginal 25 -> 15 us against 256 threads that read the cell twice).
+// 1024 threads for the small meshes too would keep sixteen wavefronts busy with the sums of a few values
+// each, two cells to a CU: 4000 cells of N = 8 85 against 15 us, 1000 of N = 16 26 against 11, 1000 of N = 20
+// 33 against 21.  A batch of several such kinds takes one launch of 1024 threads while the cells that
+// want fewer fit the chip at once (60 N = 8 and 60 N = 24 cells 10.6 us, 14 in two launches), beyond
+// that a launch for each kind, which passes over the other cells (521 N = 16, 313 N = 24
+// and 190 N = 32 cells 46 and 45 us; 4000 N = 8 and one N = 32 95 and 35).
 // ---------------------------------------------------------------------------
-constexpr int kMomThreads = 1024;
-template <int n>
-__device__ inline void block_sums(double (&x)[n], double (*red)[kMomThreads / 64]) {
-    constexpr int W = kMomThreads / 64;
+__host__ __device__ constexpr int mom_threads(int N) { return N <= 16 ? 256 : N <= 20 ? 512 : 1024; }
+template <int T, int n>
+__device__ inline void block_sums(double (&x)[n], double (*red)[T / 64]) {
+    constexpr int W = T / 64;
 #pragma unroll
     for (int i = 0; i < n; ++i) x[i] = wave_sum(x[i]);
     if ((threadIdx.x & 63) == 0) {
@@ -271,20 +280,26 @@ __device__ inline void block_sums(double (&x)[n], double (*red)[kMomThreads / 64
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < n; ++i) {
-        x[i] = red[i][threadIdx.x % W];
+        if constexpr (W <= 4) {
+            x[i] = red[i][0];
 #pragma unroll
-        for (int o = W / 2; o > 0; o >>= 1) x[i] += __shfl_xor(x[i], o);
+            for (int w = 1; w < W; ++w) x[i] += red[i][w];
+        } else {
+            x[i] = red[i][threadIdx.x % W];
+#pragma unroll
+            for (int o = W / 2; o > 0; o >>= 1) x[i] += __shfl_xor(x[i], o);
+        }
     }
 }
 
-template <int N>
+template <int N, int T>
 __device__ __forceinline__ void moments_of(const double *__restrict__ F, double dv, double *__restrict__ o,
-                                           double (*red)[kMomThreads / 64]) {
-    constexpr int M = N * N * N, PER = (M + kMomThreads - 1) / kMomThreads, h = N / 2;
+                                           double (*red)[T / 64]) {
+    constexpr int M = N * N * N, PER = (M + T - 1) / T, h = N / 2;
     double x[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const int k = threadIdx.x + i * kMomThreads;
+        const int k = threadIdx.x + i * T;
         x[i] = k < M ? F[k] : 0.0;
     }
     // (each pass recomputes its indices from an opaque copy of the thread index: kept live they spill)
@@ -293,26 +308,26 @@ __device__ __forceinline__ void moments_of(const double *__restrict__ F, double 
     asm volatile("" : "+v"(t0));
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const int k = t0 + i * kMomThreads;
+        const int k = t0 + i * T;
         if (k >= M) continue;
         a[0] += x[i];
         a[1] = fma(dv * (k / (N * N) - h), x[i], a[1]);
         a[2] = fma(dv * ((k / N) % N - h), x[i], a[2]);
         a[3] = fma(dv * (k % N - h), x[i], a[3]);
     }
-    block_sums(a, red);
+    block_sums<T>(a, red);
     const double rho = a[0], u1 = a[1] / rho, u2 = a[2] / rho, u3 = a[3] / rho;
     double e[1] = {0.0};
     int t1 = threadIdx.x;
     asm volatile("" : "+v"(t1));
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const int k = t1 + i * kMomThreads;
+        const int k = t1 + i * T;
         if (k >= M) continue;
         const double w1 = dv * (k / (N * N) - h) - u1, w2 = dv * ((k / N) % N - h) - u2, w3 = dv * (k % N - h) - u3;
         e[0] = fma(w1 * w1 + w2 * w2 + w3 * w3, x[i], e[0]);
     }
-    block_sums(e, red + 4);
+    block_sums<T>(e, red + 4);
     if (threadIdx.x == 0) {
         o[0] = rho * dv * dv * dv;
         o[1] = u1;
@@ -322,16 +337,21 @@ __device__ __forceinline__ void moments_of(const double *__restrict__ F, double 
     }
 }
 
-__global__ void __launch_bounds__(kMomThreads) k_cell_moments(const double *__restrict__ f, const long long *__restrict__ off,
-                                                              const int *__restrict__ nn, const double *__restrict__ dvs,
-                                                              double *__restrict__ mom) {
-    __shared__ double red[5][kMomThreads / 64];
-    const int c = blockIdx.x;
+// the cells of the meshes N = n_lo .. n_hi
+template <int T>
+__global__ void __launch_bounds__(T) k_cell_moments(int n_lo, int n_hi, const double *__restrict__ f,
+                                                    const long long *__restrict__ off, const int *__restrict__ nn,
+                                                    const double *__restrict__ dvs, double *__restrict__ mom) {
+    __shared__ double red[5][T / 64];
+    const int c = blockIdx.x, N = nn[c];
+    if (N < n_lo || N > n_hi) return;
     const double *F = f + off[c];
     double *o = mom + 5 * (size_t)c;
-    switch (nn[c]) {
-#define BZ_MOM(n) \
-    case n: moments_of<n>(F, dvs[c], o, red); break;
+    switch (N) {
+#define BZ_MOM(n)                                                               \
+    case n:                                                                     \
+        if constexpr (mom_threads(n) <= T) moments_of<n, T>(F, dvs[c], o, red); \
+        break;
         BZ_MOM(8) BZ_MOM(12) BZ_MOM(16) BZ_MOM(20) BZ_MOM(24) BZ_MOM(28) BZ_MOM(32)
 #undef BZ_MOM
     }
@@ -528,10 +548,26 @@ hipError_t launch_build_e3(int N, const long long *d_row_woff, const long long *
     return hipGetLastError();
 }
 
-hipError_t launch_cell_moments(int ncells, const double *f, const long long *off, const int *nn, const double *dvs,
-                               double *mom, hipStream_t s) {
+// cells_of[N / 4]: cells of mesh N
+hipError_t launch_cell_moments(int ncells, const int *cells_of, const double *f, const long long *off, const int *nn,
+                               const double *dvs, double *mom, hipStream_t s) {
     if (ncells <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cell_moments, dim3(ncells), dim3(kMomThreads), 0, s, f, off, nn, dvs, mom);
+    int cells[3] = {0, 0, 0};   // by threads: 256, 512, 1024
+    for (int N = kMinN; N <= kMaxN; N += 4) cells[mom_threads(N) / 512] += cells_of[N / 4];
+    auto launch = [&](auto t, int n_lo, int n_hi) {
+        hipLaunchKernelGGL(k_cell_moments<t()>, dim3(ncells), dim3(t()), 0, s, n_lo, n_hi, f, off, nn, dvs, mom);
+    };
+    constexpr std::integral_constant<int, 256> small{};
+    constexpr std::integral_constant<int, 512> middle{};
+    constexpr std::integral_constant<int, 1024> large{};
+    if (cells[0] == ncells) launch(small, kMinN, 16);
+    else if (cells[1] == ncells) launch(middle, 20, 20);
+    else if (cells[0] + cells[1] <= 512) launch(large, kMinN, kMaxN);
+    else {
+        if (cells[0]) launch(small, kMinN, 16);
+        if (cells[1]) launch(middle, 20, 20);
+        if (cells[2]) launch(large, 24, kMaxN);
+    }
     return hipGetLastError();
 }
 

@@ -1584,7 +1584,10 @@ bz_status bz_project(bz_batch b, double *d_Q, void *stream) {
 
 bz_status bz_cell_moments(bz_batch b, const double *d_f, double *d_mom, void *stream) {
     if (!b || !d_f || !d_mom) return fail(BZ_EINVAL, "bz_cell_moments: NULL argument");
-    BZ_HIP(launch_cell_moments(b->n_cells, d_f, b->d_cell_off, b->d_cell_N, b->d_cell_dv, d_mom, (hipStream_t)stream),
+    int cells_of[kMaxN / 4 + 1] = {};
+    for (const Part &p : b->parts) cells_of[p.g->N / 4] += (int)p.cells.size();
+    BZ_HIP(launch_cell_moments(b->n_cells, cells_of, d_f, b->d_cell_off, b->d_cell_N, b->d_cell_dv, d_mom,
+                               (hipStream_t)stream),
            "bz_cell_moments");
     return BZ_OK;
 }

@@ -1,5 +1,5 @@
-"""Layouts that a batch's FP64 kernel and its last group take by the number of cells: the results do not
-depend on them, and a batch takes no longer than one with more cells."""
+"""Layouts and launch shapes that go by the number of cells or rows: the results do not depend on them, and a
+call takes no longer than one with more work."""
 import statistics
 
 import numpy as np
@@ -67,3 +67,48 @@ def test_fp64_half_group_takes_no_longer_than_a_whole_one(dev, N, L):
         ms[n] = _time(lambda: c.collide(f, q))
         c.close()
     assert ms[32] <= 1.1 * ms[64], ms
+
+
+# many cells of a small mesh against the same bytes in cells of a larger one (a cell is one block: up to three times)
+@pytest.mark.parametrize("N,n", [(8, 4000), (12, 1188)])
+def test_moments_of_many_small_cells(dev, N, n):
+    ms = {}
+    for mesh, cells in ((N, n), (24, n * N ** 3 // 24 ** 3)):
+        g = bz.bz_grid_init(mesh, 6.0, 1.0)
+        b = bz.bz_batch_create(np.zeros(cells, np.int32), [g], bz.BZ_MODE_PLAIN_F64)
+        f = torch.rand(cells * mesh ** 3, dtype=torch.float64, device=dev)
+        mom = torch.empty(5 * cells, dtype=torch.float64, device=dev)
+        ms[mesh] = _time(lambda: bz.bz_cell_moments(b, f, mom))
+        bz.bz_batch_free(b)
+        bz.bz_grid_free(g)
+    assert ms[N] <= 3.0 * ms[24], ms
+
+
+# one launch for all cells, a launch for each kind of mesh, and the meshes alone.  Sums of N^3 positive terms in
+# another order differ by at most N^3 2^-53 relative; the velocities are differences of such sums over v up to L.
+@pytest.mark.parametrize("spec", [((8, 3), (20, 2), (32, 2)), ((8, 600), (12, 5), (20, 40), (28, 3)), ((20, 7),), ((16, 5),)])
+def test_moments_by_kind_of_mesh(dev, spec):
+    Ls = {8: 4.0, 12: 5.0, 16: 6.0, 20: 6.0, 28: 7.5, 32: 8.0}
+    grids = [bz.bz_grid_init(N, Ls[N], 1.0) for N, _ in spec]
+    mesh_of = np.repeat(np.arange(len(spec)), [n for _, n in spec])
+    rng = np.random.default_rng(5)
+    rng.shuffle(mesh_of)
+    cells = [rng.uniform(0.1, 1.0, (spec[m][0],) * 3) for m in mesh_of]
+    b = bz.bz_batch_create(mesh_of.astype(np.int32), grids, bz.BZ_MODE_PLAIN_F64)
+    f = torch.from_numpy(np.concatenate([c.ravel() for c in cells])).to(dev)
+    mom = torch.full((5 * len(cells),), float("nan"), dtype=torch.float64, device=dev)
+    bz.bz_cell_moments(b, f, mom)
+    got = mom.cpu().numpy().reshape(-1, 5)
+    for c, m, o in zip(cells, mesh_of, got):
+        N, L = spec[m][0], Ls[spec[m][0]]
+        dv, tol = 2 * L / N, 4 * N ** 3 * 2.0 ** -53
+        v = dv * (np.arange(N) - N // 2)
+        rho = c.sum()
+        u = [np.tensordot(c, v, axes=([d], [0])).sum() / rho for d in range(3)]
+        w2 = sum((v - u[d]).reshape([-1 if e == d else 1 for e in range(3)]) ** 2 for d in range(3))
+        assert abs(o[0] - rho * dv ** 3) <= tol * rho * dv ** 3
+        assert np.max(np.abs(o[1:4] - u)) <= tol * L
+        assert abs(o[4] - (w2 * c).sum() / (3 * rho)) <= tol * 3 * L * L
+    bz.bz_batch_free(b)
+    for g in grids:
+        bz.bz_grid_free(g)
