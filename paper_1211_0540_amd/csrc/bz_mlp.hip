@@ -516,12 +516,18 @@ static hipError_t gemm(int epi, int M, int N, int K, const unsigned short *A, in
     dim3 grid((N + TBN - 1) / TBN, (M + TBM - 1) / TBM);
     const int tiles = (int)(grid.x * grid.y);
     int split = 1;
+    bool reduce = false;
     if (tiles < 128) {
         split = std::min(std::min(kMaxSplit, K / 256), (256 + tiles - 1) / tiles);
         const size_t cap = wv.split_floats / ((size_t)M * N);
         if ((size_t)split > cap) split = (int)cap;
+        // the gradient through the GELU of a few tiles goes to the reduction, be it over one slice: in the product's
+        // epilogue a lane takes 64 of them, each waiting for its input, on those few CUs only (N = 24, 96 rows,
+        // hidden 256: a backward pass 187 us by the epilogue, 162 by the reduction)
+        reduce = split >= 2 || (epi == EPI_DGELU && cap >= 1);
+        split = std::max(split, 1);
     }
-    if (split >= 2) {
+    if (reduce) {
         grid.z = split;
         hipLaunchKernelGGL(k_gemm_nt<EPI_PARTIAL>, grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, 1.f, nullptr,
                            wv.split, N, nullptr, 0);

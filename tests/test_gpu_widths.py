@@ -112,3 +112,21 @@ def test_moments_by_kind_of_mesh(dev, spec):
     bz.bz_batch_free(b)
     for g in grids:
         bz.bz_grid_free(g)
+
+
+# a hidden layer of 256 against one of 512 (its last product alone is half as long; 5% for the clock)
+@pytest.mark.parametrize("N", [16, 24])
+def test_backward_of_a_narrow_layer_takes_no_longer(dev, N):
+    rows, M, ms = 96, N ** 3, {}
+    for hidden in (256, 512):
+        net = bz.bz_mlp_create(M, hidden, M)
+        params = torch.zeros(bz.bz_mlp_param_bytes(net), dtype=torch.uint8, device=dev)
+        master = np.random.default_rng(3).standard_normal(bz.bz_mlp_param_count(net)) * 0.02
+        bz.bz_mlp_set_params(net, params, master.astype(np.float32))
+        x = torch.randn(rows, M, device=dev).to(torch.bfloat16).view(torch.int16)
+        y = torch.randn(rows, M, device=dev)
+        work = torch.zeros(bz.bz_mlp_workspace_bytes(net, rows), dtype=torch.uint8, device=dev)
+        grad, loss = torch.zeros(master.size, device=dev), torch.zeros(1, device=dev)
+        ms[hidden] = _time(lambda: bz.bz_mlp_backward(net, params, x, y, rows, grad, loss, work))
+        bz.bz_mlp_free(net)
+    assert ms[256] <= 1.05 * ms[512], ms
