@@ -976,14 +976,26 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         }
         std::stable_sort(conv.begin(), conv.end(), [](const Costed &x, const Costed &y) { return x.cost > y.cost; });
         std::stable_sort(core.begin(), core.end(), [](const int4 &x, const int4 &y) { return x.w - x.z > y.w - y.z; });
-        // queue of every item: the groups of all meshes in a line, each as long as its FP32 cost, cut into
+        // what an item takes of the chip when all of it is busy: its cost, but a pass of two steps on 32 lanes of cells
+        // takes 1.82 steps (launches of 32 / 64 cells: N = 20 150 / 153, 24 297 / 331, 28 662 / 714, 32 1179 / 1311 us).
+        // Counted as one step it left the XCDs of such a group with twice their share (160 cells of N = 32 4.52 ms
+        // an evaluation, 4.00 now; 224 cells 6.29 and 5.48).  The order of the items stays by their
+        // passes: by their time, narrow items first, some batches are 2% faster and as many slower.
+        auto length = [&](const Costed &x) {
+            const Part &p = b->parts[(x.it.y >> 24) & 0xf];
+            return (double)x.cost * (x.it.x == p.tail.g && p.tail.lw == 5 ? 1.82 : 1.0);
+        };
+        // queue of every item: the groups of all meshes in a line, each as long as its FP32 items, cut into
         // kMultiQueues equal lengths; a group's items, longest first, go to that one of its queues with
         // the most of its length left.  Queues pay where the fhat rows of the groups, a narrow one's by its
-        // lanes, are beyond what the L2s hold of them: from three groups and 13 MB on (one queue / eight,
-        // Strang steps: 256 N = 24 cells, 28 MB, 2.77 / 2.71 ms; 192 of N = 28, 34 MB, 4.61 / 4.46; 400 of N = 16,
-        // 13.1 MB, 0.93 / 0.90; the uneven batch 13.10 / 12.94 per Heun step).  Below, a wavefront's pops of
-        // seven empty queues at the end cost more: 192 of N = 20, 12.3 MB, 1.01 / 1.04; 158 of N = 12,
-        // 2.2 MB, 0.29 / 0.36; two groups, 72 of N = 24, 1.03 / 1.07
+        // lanes, are beyond what the L2s hold of them: from three groups and 13 MB on (one queue / eight, us an
+        // evaluation: N = 16 400 cells, 13.1 MB, 414 / 402; 521 502 / 477; N = 20 270 613 / 589; N = 24 144, 15.9 MB,
+        // 839 / 819; 160, 17.7 MB, 956 / 952; 192 1003 / 988; 260 1366 / 1337; N = 28 192 2209 / 2142; N = 32 190 4139 / 4117; the
+        // uneven batch 6304 / 6275).  Below, the pops of seven empty queues by every wavefront at the end cost more: N = 12
+        // 600 cells, 8.3 MB, 224 / 231; N = 16 392, 12.8 MB, 394 / 397; N = 20 192, 12.3 MB, 457 / 470; two groups, 72 of N = 24, 515 / 535.
+        // The bytes stand for the time of the launch too, which the pops are a part of, so the line is not sharp: on its upper
+        // side 129 cells of N = 24, 14.6 MB, 739 / 746, and three groups of which one is narrow beside larger
+        // ones, 208 of N = 32 4816 / 4990, 16 x 64, 24 x 64 and 32 x 20 cells 1774 / 1808
         std::vector<int> first(b->parts.size() + 1, 0);
         for (size_t mi = 0; mi < b->parts.size(); ++mi) first[mi + 1] = first[mi] + b->parts[mi].groups;
         const int ng = first.back();
@@ -997,8 +1009,8 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         std::vector<double> len(ng, 0.0);
         double total = 0.0;
         for (const Costed &x : conv) {
-            len[gid(x.it)] += (double)x.cost;
-            total += (double)x.cost;
+            len[gid(x.it)] += length(x);
+            total += length(x);
         }
         std::vector<std::vector<double>> left(ng, std::vector<double>(nq, 0.0));
         double at = 0.0;
@@ -1016,7 +1028,7 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         std::vector<double> core_len(ng, 0.0);
         for (const int4 &x : core) core_len[gid(x)] += (double)(x.w - x.z);
         std::vector<std::vector<int4>> qconv(nq), qcore(nq);
-        for (const Costed &x : conv) qconv[deal(left[gid(x.it)], (double)x.cost)].push_back(x.it);
+        for (const Costed &x : conv) qconv[deal(left[gid(x.it)], length(x))].push_back(x.it);
         for (const int4 &x : core) {
             const int g = gid(x);
             qcore[deal(core_left[g], (double)(x.w - x.z) * len[g] / std::max(1.0, core_len[g]))].push_back(x);

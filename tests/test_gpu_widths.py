@@ -130,3 +130,39 @@ def test_backward_of_a_narrow_layer_takes_no_longer(dev, N):
         ms[hidden] = _time(lambda: bz.bz_mlp_backward(net, params, x, y, rows, grad, loss, work))
         bz.bz_mlp_free(net)
     assert ms[256] <= 1.05 * ms[512], ms
+
+
+# a queue per XCD over several meshes, with narrow last groups of 8, 16 and 32 lanes and whole ones, and on both sides of
+# the line in bytes, against the per-mesh launches of the same accumulation variant: bitwise
+@pytest.mark.parametrize("spec", [((16, 80), (20, 90), (24, 72), (32, 100)), ((24, 70), (32, 150)), ((16, 392),), ((16, 393),),
+                                  ((32, 160),)])
+def test_queues_over_meshes_are_bitwise_the_per_mesh_launches(dev, spec):
+    Ls = {16: 6.0, 20: 6.0, 24: 7.0, 32: 8.0}
+    base = {N: W.random_smooth_cells(8, N, Ls[N], seed=800 + N, umax=0.5) for N, _ in spec}
+    mesh_of = np.repeat(np.arange(len(spec)), [n for _, n in spec])
+    np.random.default_rng(6).shuffle(mesh_of)
+    cells = [base[spec[m][0]][i % 8] * (1.0 + i / 1024) for i, m in enumerate(mesh_of)]
+    out = []
+    for per_mesh in (False, True):
+        c = bz.Collision([(N, Ls[N], 1.0) for N, _ in spec], mesh_of, "batched_f32", weights_cache=_WCACHE,
+                         per_mesh=per_mesh)
+        assert bz.bz_batch_one_launch(c.batch) != per_mesh
+        c.set_variant(12)
+        f = torch.from_numpy(c.pack(cells)).to(dev)
+        for _ in range(2):
+            out.append(c.collide(f).cpu().numpy())
+        c.close()
+    assert np.all(np.isfinite(out[0]))
+    for o in out[1:]:
+        assert np.array_equal(out[0], o)
+
+
+# three groups and 32 cells against four groups: 3.5 times a group's work at most in the time of 4 (6% for the clock)
+def test_a_half_group_does_not_hold_up_the_queues(dev):
+    base, ms = W.random_smooth_cells(1, 32, 8.0, seed=732, umax=0.5)[0], {}
+    for n in (224, 256):
+        c, f = _batch(32, 8.0, [base] * n, "batched_f32", dev)
+        q = torch.empty_like(f)
+        ms[n] = _time(lambda: c.collide(f, q))
+        c.close()
+    assert ms[224] <= 1.06 * ms[256], ms
