@@ -222,8 +222,9 @@ bz_status bz_batch_create(int n_cells, const int32_t *grid_of_cell, int n_grids,
  *                      ordered by cost, each naming its mesh (the variant
  *                      with FOLD 16 and two interleaved partials for every
  *                      mesh), and the FP64 core items spread through the
- *                      first 3/5 of it; a last group of at most 32 cells takes
- *                      several steps at once, with bitwise the same results;
+ *                      first 3/5 of it; a last group of at most 32 cells (16
+ *                      at N = 32) takes several steps at once, with bitwise
+ *                      the same results;
  *                      the transforms stay one launch per mesh and pass.  bz_batch_autotune may switch a batch
  *                      to the per-mesh launches when they are faster.
  *   BZ_BATCH_FINE_SPLIT  cut the rows into work items small enough for the

@@ -311,7 +311,8 @@ struct CoreFill {
     const int *disk_idx;   // device, N*N
     int nD, r, r2;
 };
-// The last group of a mesh's cells, when it holds at most half of 64 and runs in the narrow layout:
+// The last group of a mesh's cells, when it holds at most half of 64 (a quarter on the largest meshes) and runs in the
+// narrow layout:
 // W = 2^lw cells (4 to 32), element (k, cell) of its buffers at k W + cell from the group's base;
 // g = -1: none.  The core lines keep 64 cells.
 struct NarrowTail {

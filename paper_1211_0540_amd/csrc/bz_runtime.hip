@@ -767,13 +767,15 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         if (p.cells.empty()) continue;
         p.groups = (int)((p.cells.size() + kWave - 1) / kWave);
         // a last group of at most 32 cells: W = 4, 8, 16 or 32 lanes hold its cells in the one launch
-        // and the FP64 kernel, which take 64 / W steps of a row at once (FP32 items of one group, W = 64 / 32 / 4: N = 32
-        // 1.41 / 1.24 / 0.30 ms, N = 24 345 / 286 / 104 us, N = 16 80 / 74 / 44 us; above 32 cells
-        // there is no second step to take).  In FP64 from N = 28 on W = 32 does not pay: two rows of a cell
-        // take half the registers or more, and two steps at once cost more than one after the other (32 cells
-        // narrow / wide: N = 28 2.06 / 1.80 ms, N = 32 4.34 / 2.93; 16 cells 1.21 / 1.80 and 2.34 / 2.93; N = 24 0.68 / 0.70)
+        // and the FP64 kernel, which take 64 / W steps of a row at once (launches of one group in FP32, 64 / 32 / 16 / 8 / 4
+        // cells: N = 32 1311 / 1179 / 668 / 440 / 316 us, N = 24 331 / 297 / 182 / 144 / 115, N = 16 87 / 85 / 66 / 66 / 60;
+        // above 32 cells there is no second step to take).  On the largest meshes two rows of a cell fill the
+        // registers and two steps at once cost as much as one after the other or more, so W = 32 ends below N = 32, in
+        // FP64 below N = 28 (evaluations of 32 cells, narrow / wide: FP32 N = 28 759 / 778 us, N = 32 1303 / 1286, and 224
+        // cells 5.45 / 5.23 ms; FP64 N = 24 0.68 / 0.70 ms, N = 28 2.06 / 1.80, N = 32 4.34 / 2.93; 16 cells 1.21 / 1.80 and
+        // 2.34 / 2.93)
         const int rest = (int)(p.cells.size() % kWave);
-        const int most = mode == BZ_MODE_BATCHED_F64 && p.g->N >= 28 ? kWave / 4 : kWave / 2;
+        const int most = p.g->N >= (mode == BZ_MODE_BATCHED_F64 ? 28 : 32) ? kWave / 4 : kWave / 2;
         if (rest >= 1 && rest <= most) {
             p.tail.g = p.groups - 1;
             p.tail.lw = 2;
@@ -977,9 +979,9 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         std::stable_sort(conv.begin(), conv.end(), [](const Costed &x, const Costed &y) { return x.cost > y.cost; });
         std::stable_sort(core.begin(), core.end(), [](const int4 &x, const int4 &y) { return x.w - x.z > y.w - y.z; });
         // what an item takes of the chip when all of it is busy: its cost, but a pass of two steps on 32 lanes of cells
-        // takes 1.82 steps (launches of 32 / 64 cells: N = 20 150 / 153, 24 297 / 331, 28 662 / 714, 32 1179 / 1311 us).
-        // Counted as one step it left the XCDs of such a group with twice their share (160 cells of N = 32 4.52 ms
-        // an evaluation, 4.00 now; 224 cells 6.29 and 5.48).  The order of the items stays by their
+        // takes 1.82 steps (launches of 32 / 64 cells: N = 20 150 / 153, 24 297 / 331, 28 662 / 714 us).
+        // Counted as one step it left the XCDs of such a group with twice their share (160 cells of N = 28 2.20 ms
+        // an evaluation, 2.01 now; 224 cells 3.01 and 2.70).  The order of the items stays by their
         // passes: by their time, narrow items first, some batches are 2% faster and as many slower.
         auto length = [&](const Costed &x) {
             const Part &p = b->parts[(x.it.y >> 24) & 0xf];
@@ -995,7 +997,7 @@ bz_status bz_batch_create_ex(int n_cells, const int32_t *grid_of_cell, int n_gri
         // 600 cells, 8.3 MB, 224 / 231; N = 16 392, 12.8 MB, 394 / 397; N = 20 192, 12.3 MB, 457 / 470; two groups, 72 of N = 24, 515 / 535.
         // The bytes stand for the time of the launch too, which the pops are a part of, so the line is not sharp: on its upper
         // side 129 cells of N = 24, 14.6 MB, 739 / 746, and three groups of which one is narrow beside larger
-        // ones, 208 of N = 32 4816 / 4990, 16 x 64, 24 x 64 and 32 x 20 cells 1774 / 1808
+        // ones, 208 of N = 32 4816 / 4990
         std::vector<int> first(b->parts.size() + 1, 0);
         for (size_t mi = 0; mi < b->parts.size(); ++mi) first[mi + 1] = first[mi] + b->parts[mi].groups;
         const int ng = first.back();

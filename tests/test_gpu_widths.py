@@ -157,7 +157,7 @@ def test_queues_over_meshes_are_bitwise_the_per_mesh_launches(dev, spec):
         assert np.array_equal(out[0], o)
 
 
-# three groups and 32 cells against four groups: 3.5 times a group's work at most in the time of 4 (6% for the clock)
+# three groups and a half against four: 3.5 times a group's work at most in the time of 4 (6% for the clock)
 def test_a_half_group_does_not_hold_up_the_queues(dev):
     base, ms = W.random_smooth_cells(1, 32, 8.0, seed=732, umax=0.5)[0], {}
     for n in (224, 256):
