@@ -25,7 +25,8 @@
 //   its pass of the conjugate-symmetric schedule (bz_internal.h): which fhat
 //   copy it reads, which weight stream and which output buffer it writes; the
 //   full-sum schedule uses pass A only.  Steps of pass A whose rows lie on a
-//   zeroed plane of its fhat copy are skipped.
+//   zeroed plane of its fhat copy (N = 32: 4.5% of them) are left out; the narrow items
+//   (narrow_item) run them.
 //
 //   FP32 variant: products, per-step partials and a running sum over FOLD
 //   steps in FP32 (the running sum takes one rounding per output and step);
@@ -151,11 +152,11 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F &
 }
 
 // cells_step with the weights of the step at w (global memory, wavefront-uniform) through scalar
-// registers; `cur` holds the first chunk of the step and, on return, that of the next
+// registers; `cur` holds the first chunk of the step and, on return, that of the next, whose weights are at wn
 template <typename T, int N, int SPLIT, int CW>
 __device__ __forceinline__ void cells_step_scalar(const typename cplx<T>::t (&mv)[N], const typename cplx<T>::t (&jv)[N],
-                                                  const T *w, WeightChunk<T, CW> &cur, T (&pr)[N], T (&pi)[N]) {
-    constexpr int h = N / 2;
+                                                  const T *w, const T *wn, WeightChunk<T, CW> &cur, T (&pr)[N], T (&pi)[N]) {
+    constexpr int h = N / 2, PS = 3 * N * N / 4;
     WeightChunk<T, CW> nxt;
     static_for(std::make_integer_sequence<int, N>{}, [&](auto K) {
         constexpr int k3 = K;
@@ -170,7 +171,7 @@ __device__ __forceinline__ void cells_step_scalar(const typename cplx<T>::t (&mv
                 if (t > 0) cur = nxt;
                 __builtin_amdgcn_sched_barrier(0);
                 __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the current chunk is here
-                nxt = load_chunk<T, CW>(w + t + CW);
+                nxt = load_chunk<T, CW>(t + CW < PS ? w + t + CW : wn);
                 __builtin_amdgcn_sched_barrier(0);
             }
             const T wt = cur.v[t % CW];
@@ -232,6 +233,42 @@ __device__ __forceinline__ void seek_step(int k1, int k2, int s0, int &m1, int &
     m2 = lo2 + s0;
 }
 
+// The steps of a row from step s0 on.  With `cut` (pass A on the plane-zeroed copy, rows k2 < N/2)
+// those with m2 = 0 or j2 = 0, whose products are all zero, are left out: per m1 the first and, below the
+// diagonal, the last (evaluations with / without them: FP32 N = 32 128 cells 2.75 / 2.71 ms, 190 4.09 / 4.00, N = 28 128 1.475 / 1.433;
+// FP64 N = 24 128 1.291 / 1.245, N = 32 190 8.41 / 8.20).
+template <int N>
+struct StepWalk {
+    int k1, k2, lo2, m1, m2, s;
+    bool cut;
+    __device__ StepWalk(int k1_, int k2_, int s0, bool cut_) : k1(k1_), k2(k2_), lo2(axis_lo(N, k2_)), s(s0), cut(cut_) {
+        seek_step<N>(k1, k2, s0, m1, m2);
+        skip();
+    }
+    __device__ void next() {
+        ++s;
+        if (++m2 > cells_m2_last(N, k1, k2, m1)) {
+            ++m1;
+            m2 = lo2;
+        }
+        skip();
+    }
+
+  private:
+    __device__ void skip() {
+        if (!cut) return;
+        if (m2 == k2 + N / 2) {
+            ++m1;
+            m2 = 0;
+            ++s;
+        }
+        if (m2 == 0) {
+            m2 = 1;
+            ++s;
+        }
+    }
+};
+
 // The pass of an item (wavefront-uniform): its fhat copy, weights and output buffer.
 __device__ __forceinline__ ConvPass pick_pass(const ConvPasses &ps, int pass) {
     ConvPass c = ps.p[0];
@@ -273,7 +310,8 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
         for (int t = 0; t < N; ++t) out[t * kWave] = make_double2(0.0, 0.0);
         return;
     }
-    const float *w = (const float *)cp.w + cp.row_woff[r] + (long long)s0 * PS;
+    StepWalk<N> at(k1, k2, s0, WP == 3 && cp.zero_planes && k2 < h);
+    const float *w = (const float *)cp.w + cp.row_woff[r] + (long long)(at.s < s1 ? at.s : s0) * PS;
     if constexpr (WP == 3) w = uniform_ptr(w);
     const float2 *G = fh + cp.fh_off + (size_t)g * M * kWave;   // this group's fhat (copy of the pass)
     const float2 *F = G + lane;
@@ -322,26 +360,20 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
         prefetch_weights<RCH>(G + (size_t)(((k1 + h - a1) * N + (k2 + h - a2)) * N) * kWave, rl + RCH * 1024);
     };
 
-    int m1, m2;
-    seek_step<N>(k1, k2, s0, m1, m2);
-    const int lo2 = axis_lo(N, k2);
     constexpr int CW = weight_chunk<float, N>();
     WeightChunk<float, CW> wc;
     if constexpr (WP == 3) wc = load_chunk<float, CW>(w);
     else prefetch_weights<CH>(w, wl);
-    if (RP && s0 < s1) prefetch_rows(m1, m2);
+    if (RP && s0 < s1) prefetch_rows(at.m1, at.m2);
     if (WP != 3) __builtin_amdgcn_s_waitcnt(0);
-    int buf = 0, nst = 0;
-    for (int s = s0; s < s1; ++s) {
-        const int j1 = k1 + h - m1, j2 = k2 + h - m2;
-        // on a plane-zeroed copy a step with m2 = 0 or j2 = 0 has only zero products
-        const bool live = !cp.zero_planes || (m2 != 0 && j2 != 0);
-        // (m1, m2) of the next step in the row's order
-        int n1 = m1, n2 = m2 + 1;
-        if (n2 > cells_m2_last(N, k1, k2, m1)) {
-            ++n1;
-            n2 = lo2;
-        }
+    int buf = 0, nst = at.s - s0;
+    while (at.s < s1) {
+        const int m1 = at.m1, m2 = at.m2, j1 = k1 + h - m1, j2 = k2 + h - m2;
+        // on a plane-zeroed copy a step with m2 = 0 or j2 = 0 has only zero products (the scalar
+        // weights leave it out, the others its arithmetic)
+        const bool live = WP == 3 || !cp.zero_planes || (m2 != 0 && j2 != 0);
+        StepWalk<N> nx = at;
+        nx.next();
         float2 mv[N], jv[N];
         if (RP) {
 #pragma unroll
@@ -351,7 +383,7 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
                 jv[t] = make_float2(rbuf[b], rbuf[b + 1]);
             }
             __builtin_amdgcn_s_waitcnt(0);        // rows are in registers: the buffer is free
-            if (s + 1 < s1) prefetch_rows(n1, n2);
+            if (nx.s < s1) prefetch_rows(nx.m1, nx.m2);
         } else {
             load_row<float, N>(F + (size_t)((m1 * N + m2) * N) * kWave, mv);
             load_row<float, N>(F + (size_t)((j1 * N + j2) * N) * kWave, jv);
@@ -363,11 +395,13 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
         } else if (WP == 3) {
             // the next step's weights pulled into L2 (64 bytes a lane, the LDS copy is discarded)
             constexpr int WL = (PS * 4 + 4095) / 4096;
+            const float *const wn = w + (nx.s < s1 ? nx.s - at.s : 1) * PS;
 #pragma unroll
             for (int c = 0; c < WL; ++c)
-                __builtin_amdgcn_global_load_lds((const void *)((const char *)(w + PS) + lane * 64 + c * 4096),
+                __builtin_amdgcn_global_load_lds((const void *)((const char *)wn + lane * 64 + c * 4096),
                                                  (void __attribute__((address_space(3))) *)rl, 4, 0, 0);
-            cells_step_scalar<float, N, SPLIT, CW>(mv, jv, w, wc, pr, pi);
+            cells_step_scalar<float, N, SPLIT, CW>(mv, jv, w, wn, wc, pr, pi);
+            w = wn;
         } else if (WP == 1) {
             // next step's weights pulled into L2 (the LDS copy is discarded); this
             // step's weights, pulled last step, are read through the scalar cache
@@ -379,14 +413,15 @@ __device__ __forceinline__ void cells_f32_item(const float2 *__restrict__ fh, do
             prefetch_weights<CH>(w + PS, wl + CH * 1024);
             if (live) cells_step<float, N, SPLIT>(mv, jv, w, pr, pi);
         }
-        w += PS;
+        if (WP != 3) w += PS;
         buf ^= 1;
-        if (++nst == FOLD) {
+        // steps left out count, so that a sum is folded where it is without
+        nst += nx.s - at.s;
+        if (nst >= FOLD) {
             fold();
-            nst = 0;
+            nst -= FOLD;
         }
-        m1 = n1;
-        m2 = n2;
+        at = nx;
         if (WP != 3) __builtin_amdgcn_s_waitcnt(0);
     }
     fold();
@@ -432,6 +467,8 @@ k_conv_cells_f32(const float2 *__restrict__ fh, const int4 *__restrict__ items, 
 // LDS: [N values][64 lanes] partials, [2N values][W cells] running sums (W <= 32).  FP64 items (one partial per output and step, no fold) take the same
 // form at half the read-ahead (one N = 32 cell: 0.97 against
 // 2.9 ms an evaluation).
+// The steps on a zeroed plane (StepWalk) are run here: with them left out FP32 groups were up to 2% faster at W = 4 and 2%
+// slower at W = 32, with the wide items of the launch 1% slower; FP64 5% faster at N = 24 and 28, 5% slower at N = 32.
 // REMAT: what is the same in every pass (LDS addresses, row strides) is computed again in each: kept
 // live it takes registers that the wide body of the same kernel is short of (FP64, N = 32: 16
 // cells 2.77 -> 2.34 ms an evaluation).
@@ -887,14 +924,12 @@ k_conv_cells_f64(const double2 *__restrict__ fh, const int4 *__restrict__ items,
             narrow_item<double, N, (N >= 16 && FORM == kMixedGroups)>(fh, qh, cp, item, nt.lw, wl, sink);
             continue;
         }
-        const double *w = (const double *)cp.w + cp.row_woff[r] + (long long)s0 * PS;
+        StepWalk<N> at(k1, k2, s0, kScalar && __builtin_amdgcn_readfirstlane(cp.zero_planes) && k2 < h);
+        const double *w = (const double *)cp.w + cp.row_woff[r] + (long long)(at.s < s1 ? at.s : s0) * PS;
         const double2 *F = fh + cp.fh_off + (size_t)g * M * kWave + lane;
         double pr[N], pi[N];
 #pragma unroll
         for (int t = 0; t < N; ++t) pr[t] = pi[t] = 0.0;
-        int m1, m2;
-        seek_step<N>(k1, k2, s0, m1, m2);
-        const int lo2 = axis_lo(N, k2);
         WeightChunk<double, CW> wc;
         if constexpr (kScalar) {
             w = uniform_ptr(w);
@@ -904,28 +939,29 @@ k_conv_cells_f64(const double2 *__restrict__ fh, const int4 *__restrict__ items,
             __builtin_amdgcn_s_waitcnt(0);
         }
         int buf = 0;
-        for (int s = s0; s < s1; ++s) {
-            const int j1 = k1 + h - m1, j2 = k2 + h - m2;
+        while (at.s < s1) {
+            const int m1 = at.m1, m2 = at.m2, j1 = k1 + h - m1, j2 = k2 + h - m2;
+            StepWalk<N> nx = at;
+            nx.next();
             if constexpr (!kScalar) prefetch_weights<CH>(w + PS, wl + (buf ^ 1) * CH * 1024);
             double2 mv[N], jv[N];
             load_row<double, N>(F + (size_t)((m1 * N + m2) * N) * kWave, mv);
             load_row<double, N>(F + (size_t)((j1 * N + j2) * N) * kWave, jv);
             if constexpr (kScalar) {
                 // the next step's weights pulled into L2 (64 bytes a lane, the LDS copy is discarded)
+                const double *const wn = w + (nx.s < s1 ? nx.s - at.s : 1) * PS;
 #pragma unroll
                 for (int c = 0; c < WL; ++c)
-                    __builtin_amdgcn_global_load_lds((const void *)((const char *)(w + PS) + lane * 64 + c * 4096),
+                    __builtin_amdgcn_global_load_lds((const void *)((const char *)wn + lane * 64 + c * 4096),
                                                      (void __attribute__((address_space(3))) *)sink, 4, 0, 0);
-                cells_step_scalar<double, N, 1, CW>(mv, jv, w, wc, pr, pi);
+                cells_step_scalar<double, N, 1, CW>(mv, jv, w, wn, wc, pr, pi);
+                w = wn;
             } else if (!cp.zero_planes || (m2 != 0 && j2 != 0)) {
                 cells_step<double, N, 1>(mv, jv, (const lds_double *)(wl + buf * CH * 1024), pr, pi);
             }
-            w += PS;
+            if constexpr (!kScalar) w += PS;
             buf ^= 1;
-            if (++m2 > cells_m2_last(N, k1, k2, m1)) {
-                ++m1;
-                m2 = lo2;
-            }
+            at = nx;
             if constexpr (!kScalar) __builtin_amdgcn_s_waitcnt(0);
         }
 #pragma unroll

@@ -347,7 +347,7 @@ struct ConvPass {
     long long out_off;           // first output buffer written by the pass
     const void *w;               // weight stream
     const long long *row_woff;   // device, N*N offsets of the rows in w (elements)
-    int zero_planes;             // fhat copy has its k_d = 0 planes zeroed: skip steps with m2 = 0 or j2 = 0
+    int zero_planes;             // fhat copy has its k_d = 0 planes zeroed: steps with m2 = 0 or j2 = 0 add nothing
     int row0;                    // first row the pass writes: row r goes to slot r - row0
     long long gstride;           // complex elements per group in the pass's output buffer
     long long pstride;           // complex elements between its partial-sum buffers
