@@ -462,8 +462,10 @@ k_conv_cells_f32(const float2 *__restrict__ fh, const int4 *__restrict__ items, 
 // N=32 cell: 0.30 against 1.41 ms).  The partials go to LDS, half a row at a time, and are then added
 // to the running sums in step order, so the sums are bitwise those of a 64-cell group: a cell's
 // result does not depend on the width of its group.  The weights are read from memory once per
-// 16 bytes and lane (a step's weights are contiguous), kRing reads ahead of their use; that is
-// what bounds the pass: 16 cycles of the CU's L1 per 24 operations, as the broadcasts of LDS.
+// 16 bytes and lane (a step's weights are contiguous), kRing reads ahead of their use.  These reads take 16
+// cycles of the CU's L1 per 24 operations, as the broadcasts of LDS: 56 of the 316 us of a launch for one
+// N = 32 cell, so a pass is bound by its latencies (the row loads before it, the two flushes through
+// LDS in it, at W = 4 a fold in every pass) rather than by a rate.
 // LDS: [N values][64 lanes] partials, [2N values][W cells] running sums (W <= 32).  FP64 items (one partial per output and step, no fold) take the same
 // form at half the read-ahead (one N = 32 cell: 0.97 against
 // 2.9 ms an evaluation).
@@ -789,8 +791,9 @@ k_conv_core(int N, int nD, const double2 *__restrict__ cf, const int4 *__restric
 // arithmetic of the other wavefront on the SIMD.
 // Weights by scalar loads from N = 28 on (N = 32, 190 cells: 3.9 against 4.2 ms a launch, whose
 // LDS broadcasts return 64 bytes a cycle and CU, less than the four SIMDs consume); below, where
-// a step is short (N = 16: 768 pairs), the wait for each chunk costs as much as the broadcasts
-// (72 to 521 cells within 1%, one N = 16 cell 2% slower).
+// a step is short (N = 16: 192 pairs, N = 32: 768), the wait for each chunk costs about what the broadcasts
+// do: N = 16 72 to 521 cells within 1%, one cell 2% slower; N = 24 256 cells 2% faster by scalar loads (2.65
+// against 2.71 ms a Strang step), 72 cells, of which 8 are narrow, 3% slower (1.06 against 1.03).
 template <int N>
 constexpr int multi_weight_path() {
     return N >= 28 ? 3 : 0;
@@ -882,8 +885,8 @@ k_conv_cells_f32_multi(const int4 *__restrict__ items, const MultiQueues mq, uns
 // ---------------------------------------------------------------------------
 // The weights arrive by scalar loads from N = 24 on (190 N = 32 cells 10.0 -> 8.0 ms a launch, 200 N = 24
 // cells 2.76 -> 2.41 ms an evaluation): with one wavefront per SIMD the broadcast LDS reads take 32 cycles per
-// pair and CU, the FP64 operations of the four SIMDs 24.  Below, two or more wavefronts share a SIMD and the
-// wait for a chunk of 16 weights costs more (N = 20 1.06 against 1.12 ms, N = 16 330 against 352 us).
+// pair and CU, the FP64 operations of the four SIMDs 24.  Below, the steps are short and the
+// wait for a chunk of 16 weights costs more (N = 20, one wavefront per SIMD too, 1.06 against 1.12 ms, N = 16 330 against 352 us).
 // Forms of the kernel at N = 16, by the groups of the batch.  The wide body alone takes 250 of the 256 vector
 // registers that leave two wavefronts on a SIMD, with the narrow body beside it 290 (256 cells 321 against 365 us): a batch
 // of whole groups has a kernel without the narrow body.  With whole groups and a narrow one the two are

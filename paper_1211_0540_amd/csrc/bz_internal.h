@@ -208,7 +208,7 @@ struct CoreAdd {
 // ---------------------------------------------------------------------------
 constexpr int kCoreMaxR = 8;
 __host__ __device__ constexpr int core_wstride(int r) {
-    // weights of one step, padded to whole KiB (128 doubles) for the direct-to-LDS copy
+    // weights of one step, padded to whole KiB (128 doubles): a step's 128-byte lines start on a line
     return ((2 * r + 1) * (2 * r + 1) + 127) / 128 * 128;
 }
 

@@ -467,8 +467,8 @@ struct WorkView {
     float *split;                // split-K slices
     size_t split_floats;
     float *Z1, *Z2, *Y;          // FP32
-    unsigned short *A1, *A2;     // BF16 activations
-    unsigned short *dY, *dZ;     // BF16 gradients (dZ reused for layers 2 and 1)
+    unsigned short *A1, *A2;     // BF16 activations; after the gradient of W3 the backward pass writes layer 1's dZ to A2
+    unsigned short *dY, *dZ;     // BF16 gradients of the output and of layer 2
     unsigned short *tA, *tB;     // transposes
     double *part;
     float *loss;

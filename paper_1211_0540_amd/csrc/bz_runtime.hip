@@ -444,7 +444,6 @@ struct bz_batch_s {
     int *d_cell_N = nullptr;
     double *d_cell_dv = nullptr;
     size_t ws_scratch = 0, ws_flag = 0, ws_total = 0;
-    int plain_split = 4;
     // convolution timing
     bool timing = false;
     double core_ms = 0.0;            // FP64 core launches timed at the last bz_batch_timer_read
@@ -483,7 +482,10 @@ static int mode_wkind(int mode) {
     }
 }
 static int plain_split_for(int N) {
-    // enough partial sums to give >= ~2048 single-wave blocks, bounded by the m1 band
+    // enough partial sums to give >= ~2048 blocks, at most 8 and N/2: with eight wavefronts a block that is eight
+    // rounds of the chip, whose blocks end at different times (two cells, nsplit 1 / 2 / 4 / this rule, us: FP64 N = 28
+    // 2704 / 2103 / 1761 / 1706 (6), N = 24 1575 / 908 / 792 / 706 (8), N = 16 156 / 98 / 74 / 75 (8), N = 8 48 / 42 / 40 / 40 (4);
+    // FP32 N = 24 1510 / 842 / 715 / 618, N = 16 323 / 181 / 114 / 81), and more than the buffers cost the inverse
     const int nb = N * (N / plain_rows(N));
     int s = (2048 + nb - 1) / nb;
     const int cmin = N / 2;
