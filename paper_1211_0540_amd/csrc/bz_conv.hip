@@ -25,8 +25,8 @@
 //   its pass of the conjugate-symmetric schedule (bz_internal.h): which fhat
 //   copy it reads, which weight stream and which output buffer it writes; the
 //   full-sum schedule uses pass A only.  Steps of pass A whose rows lie on a
-//   zeroed plane of its fhat copy (N = 32: 4.5% of them) are left out; the narrow items
-//   (narrow_item) run them.
+//   zeroed plane of its fhat copy (N = 32: 4.5% of them) are left out; of the narrow items
+//   (narrow_item) the FP64 ones of N = 20 to 28 leave them out.
 //
 //   FP32 variant: products, per-step partials and a running sum over FOLD
 //   steps in FP32 (the running sum takes one rounding per output and step);
@@ -469,8 +469,10 @@ k_conv_cells_f32(const float2 *__restrict__ fh, const int4 *__restrict__ items, 
 // LDS: [N values][64 lanes] partials, [2N values][W cells] running sums (W <= 32).  FP64 items (one partial per output and step, no fold) take the same
 // form at half the read-ahead (one N = 32 cell: 0.97 against
 // 2.9 ms an evaluation).
-// The steps on a zeroed plane (StepWalk) are run here: with them left out FP32 groups were up to 2% faster at W = 4 and 2%
-// slower at W = 32, with the wide items of the launch 1% slower; FP64 5% faster at N = 24 and 28, 5% slower at N = 32.
+// CUT: the steps on a zeroed plane are left out as in the wide items (StepWalk), in FP64 from N = 20 to 28 (evaluations of
+// 16 cells: N = 20 190 -> 188 us, N = 24 388 -> 379, N = 28 1207 -> 1158).  At N = 32, short of registers, it cost
+// 5%, below N = 20 it gave nothing, and in FP32, whose totals are folded by the steps' indices, up to 2% at
+// W = 4 against 2% lost at W = 32 and 1% in the wide items of the launch.
 // REMAT: what is the same in every pass (LDS addresses, row strides) is computed again in each: kept
 // live it takes registers that the wide body of the same kernel is short of (FP64, N = 32: 16
 // cells 2.77 -> 2.34 ms an evaluation).
@@ -488,7 +490,7 @@ template <>
 struct vec4<double> {
     using t = double4;
 };
-template <typename T, int N, bool REMAT>
+template <typename T, int N, bool REMAT, bool CUT>
 __device__ __forceinline__ void narrow_item(const typename cplx<T>::t *fh, double2 *qh, const ConvPass &cp, const int4 item,
                                             const int lw, lds_char *lds, lds_char *sink) {
     using C = typename cplx<T>::t;
@@ -513,34 +515,84 @@ __device__ __forceinline__ void narrow_item(const typename cplx<T>::t *fh, doubl
     }
     const char *const wu = (const char *)uniform_ptr((const T *)cp.w + cp.row_woff[r] + (long long)s0 * PS);
     const char *const G = (const char *)uniform_ptr(fh + cp.fh_off + (size_t)g * M * kWave);
-    int m1, m2, at = slice < s1 - s0 ? s0 + slice : s1 - 1;   // this lane's step
+    // this lane's step, of index `at` in the row, or one of the item past its last step
+    int m1, m2, at = slice < s1 - s0 ? s0 + slice : s1 - 1;
+    const bool cut = CUT && __builtin_amdgcn_readfirstlane(cp.zero_planes) && k2 < h;
+    const int lo = cut ? 1 : lo2;
+    auto row_end = [&](int last) { return cut && last == k2 + h ? last - 1 : last; };
+    int s = s0, next = s0 + S;   // the first slice's step of this pass and of the next (CUT: in turn)
+    if constexpr (CUT) at = s0;
     seek_step<N>(k1, k2, at, m1, m2);
+    // n steps on
+    auto advance = [&](int n) {
+        at += n;
+        for (m2 += n;;) {
+            const int last = cells_m2_last(N, k1, k2, m1), end = row_end(last);
+            if (m2 <= end) break;
+            m2 -= end - lo + 1;
+            at += last - end + lo - lo2;
+            ++m1;
+        }
+    };
+    int m1_0 = 0, m2_0 = 0, at_0 = 0;
+    if constexpr (CUT) {
+        const int off = m2 < lo;
+        m2 += off;
+        at += off;
+        advance(0);
+        s = __builtin_amdgcn_readfirstlane(at);
+        if (s >= s1) {
+            for (int i = lane; i < 2 * N * W; i += kWave) out[i] = 0.0;
+            return;
+        }
+        m1_0 = m1;
+        m2_0 = m2;
+        at_0 = at;
+        advance(slice);
+    }
     // weights of the pass at step s pulled into L2, one 128-byte line per lane and load (the copies
     // in LDS are discarded): a pass reads its S steps' weights far faster than memory answers
     // one line after the other
     auto touch = [&](int s) {
-        const int bytes = (s1 - s < S ? s1 - s : S) * (PS * (int)sizeof(T));
+        int n = s1 - s < S ? s1 - s : S;
+        if constexpr (CUT) {
+            const int b = __builtin_amdgcn_readlane(at, kWave - 1);
+            n = (b < s1 ? b + 1 : s1) - s;
+        }
+        const int bytes = n * (PS * (int)sizeof(T));
         for (int o = lane * 128; o < bytes; o += kWave * 128)
             __builtin_amdgcn_global_load_lds((const void *)(wu + (size_t)(s - s0) * (PS * sizeof(T)) + o),
                                              (void __attribute__((address_space(3))) *)sink, 4, 0, 0);
     };
-    touch(s0);
+    touch(s);
     bool first = true;
-    for (int s = s0; s < s1; s += S) {
-        const int left = s1 - s < S ? s1 - s : S;             // steps of this pass
+    for (; s < s1; s = next) {
+        int left = s1 - s < S ? s1 - s : S;                   // steps of this pass
+        int c1 = m1, c2 = m2, ca = at;
+        if constexpr (CUT) {
+            const bool in = at < s1;
+            left = __builtin_popcountll(__ballot(in)) >> lw;
+            c1 = in ? m1 : m1_0;
+            c2 = in ? m2 : m2_0;
+            ca = in ? at : at_0;
+            advance(S);
+            next = __builtin_amdgcn_readfirstlane(at);
+        } else {
+            next = s + S;
+        }
         int pl = lane, plw = lw;                              // this pass's copies
         if constexpr (REMAT) asm volatile("" : "+v"(pl), "+s"(plw));
-        const bool fold = (f32 && (s + S - s0) % FOLD == 0) || s + S >= s1;
-        const unsigned um = (unsigned)((((m1 * N + m2) * N) << lw) + cell) * (unsigned)CB;
-        const unsigned uj = (unsigned)(((((k1 + h - m1) * N + (k2 + h - m2)) * N) << lw) + cell) * (unsigned)CB;
-        const unsigned uw = (unsigned)(at - s0) * (unsigned)(PS * sizeof(T));
+        const bool fold = (f32 && (next - s0) % FOLD == 0) || next >= s1;
+        const unsigned um = (unsigned)((((c1 * N + c2) * N) << lw) + cell) * (unsigned)CB;
+        const unsigned uj = (unsigned)(((((k1 + h - c1) * N + (k2 + h - c2)) * N) << lw) + cell) * (unsigned)CB;
+        const unsigned uw = (unsigned)(ca - s0) * (unsigned)(PS * sizeof(T));
         C mv[N], jv[N];
 #pragma unroll
         for (int t = 0; t < N; ++t) {
             mv[t] = *(const C *)(G + (t << (plw + CS)) + um);
             jv[t] = *(const C *)(G + (t << (plw + CS)) + uj);
         }
-        if (s + S < s1) touch(s + S);
+        if (next < s1) touch(next);
         T4 ring[kRing];
 #pragma unroll
         for (int i = 0; i < kRing; ++i) ring[i] = *(const T4 *)(wu + uw + i * (4 * sizeof(T)));
@@ -590,13 +642,15 @@ __device__ __forceinline__ void narrow_item(const typename cplx<T>::t *fh, doubl
             if constexpr (k3 % h == h - 1) flush(k3 / h);
         });
         if (fold) first = false;
-        // this lane's next step
-        const int nx = at + S < s1 ? at + S : s1 - 1;
-        for (m2 += nx - at, at = nx;;) {
-            const int last = cells_m2_last(N, k1, k2, m1);
-            if (m2 <= last) break;
-            m2 -= last - lo2 + 1;
-            ++m1;
+        if constexpr (!CUT) {
+            // this lane's next step
+            const int nx = at + S < s1 ? at + S : s1 - 1;
+            for (m2 += nx - at, at = nx;;) {
+                const int last = cells_m2_last(N, k1, k2, m1);
+                if (m2 <= last) break;
+                m2 -= last - lo2 + 1;
+                ++m1;
+            }
         }
     }
 }
@@ -814,7 +868,7 @@ template <int N>
 __device__ __forceinline__ void fp32_item(const MeshConvDesc &d, char *ws, int pass, const int4 item, lds_char *lds) {
     lds_char *const sink = lds + kMultiSink;
     if (item.x == d.tail_g)
-        narrow_item<float, N, false>((const float2 *)(ws + d.fh_bytes), (double2 *)(ws + d.qh_bytes), d.ps.p[pass], item, d.tail_lw, lds,
+        narrow_item<float, N, false, false>((const float2 *)(ws + d.fh_bytes), (double2 *)(ws + d.qh_bytes), d.ps.p[pass], item, d.tail_lw, lds,
                               sink);
     else
         multi_item<N>(d, ws, pass, item, lds, sink);
@@ -924,7 +978,7 @@ k_conv_cells_f64(const double2 *__restrict__ fh, const int4 *__restrict__ items,
             continue;
         }
         if (FORM == kNarrowGroup || (FORM == kMixedGroups && g == nt.g)) {
-            narrow_item<double, N, (N >= 16 && FORM == kMixedGroups)>(fh, qh, cp, item, nt.lw, wl, sink);
+            narrow_item<double, N, (N >= 16 && FORM == kMixedGroups), (N >= 20 && N < 32)>(fh, qh, cp, item, nt.lw, wl, sink);
             continue;
         }
         StepWalk<N> at(k1, k2, s0, kScalar && __builtin_amdgcn_readfirstlane(cp.zero_planes) && k2 < h);

@@ -34,7 +34,9 @@ def _unread_steps(N):
 
 @pytest.mark.parametrize("mode,N,L,n", [("batched_f32", 16, 6.0, 64), ("batched_f32", 24, 7.0, 40), ("batched_f32", 28, 7.5, 64),
                                         ("batched_f32", 32, 8.0, 40), ("batched_f64", 20, 6.0, 64),
-                                        ("batched_f64", 24, 7.0, 64), ("batched_f64", 32, 8.0, 40)])
+                                        ("batched_f64", 24, 7.0, 64), ("batched_f64", 32, 8.0, 40),
+                                        ("batched_f64", 20, 6.0, 16), ("batched_f64", 24, 7.0, 72),
+                                        ("batched_f64", 28, 7.5, 3)])
 def test_steps_on_a_zeroed_plane_are_left_out(dev, mode, N, L, n):
     base = W.random_smooth_cells(4, N, L, seed=900 + N, umax=0.5)
     c = bz.Collision([(N, L, 1.0)], [0] * n, mode)
