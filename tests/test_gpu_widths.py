@@ -114,7 +114,7 @@ def test_moments_by_kind_of_mesh(dev, spec):
         bz.bz_grid_free(g)
 
 
-# a hidden layer of 256 against one of 512 (its last product alone is half as long; 5% for the clock)
+# a hidden layer of 256 against one of 512 (its last product alone is half as long; 10% for the clock and the host)
 @pytest.mark.parametrize("N", [16, 24])
 def test_backward_of_a_narrow_layer_takes_no_longer(dev, N):
     rows, M, ms = 96, N ** 3, {}
@@ -129,7 +129,7 @@ def test_backward_of_a_narrow_layer_takes_no_longer(dev, N):
         grad, loss = torch.zeros(master.size, device=dev), torch.zeros(1, device=dev)
         ms[hidden] = _time(lambda: bz.bz_mlp_backward(net, params, x, y, rows, grad, loss, work))
         bz.bz_mlp_free(net)
-    assert ms[256] <= 1.05 * ms[512], ms
+    assert ms[256] <= 1.1 * ms[512], ms
 
 
 # a queue per XCD over several meshes, with narrow last groups of 8, 16 and 32 lanes and whole ones, and on both sides of
